@@ -1,7 +1,7 @@
 // Grid reductions: conservation diagnostics (section 2.3.1) and the emergent-flux
 // loss with its seed; and the per-cell angle moments (section 2.1), reduced over each
-// cell's lanes only.  Each cell group reduces over its angles, each workgroup
-// over its cells through LDS, then two folds over the per-workgroup partials in a
+// cell's lanes only.  The lanes add their own terms over their cells, each workgroup
+// reduces over its lanes, then one or two folds over the per-workgroup partials in a
 // fixed order, so results are deterministic (no atomics).
 #include <mutex>
 
@@ -16,116 +16,147 @@ namespace {
 
 constexpr int ND = RT_NDIAG;
 
-// Block reduction of NV values held by lane 0 of each cell group; kinds: 0 sum, 1 min.
-template <int NV, int LPC>
-__device__ __forceinline__ void block_reduce_store(double (&v)[NV], const int (&kind)[NV], double *out_blk) {
-  __shared__ double sh[RT_BLOCK / LPC][NV];
-  constexpr int CPB = RT_BLOCK / LPC;
-  const int g = threadIdx.x / LPC, l = threadIdx.x % LPC;
-  if (l == 0)
-    for (int i = 0; i < NV; ++i) sh[g][i] = v[i];
+// Reduction of NV values per thread over the workgroup, in a fixed order: the xor butterfly
+// in each wave, then the four waves in turn.  Value i is a sum, or the minimum where bit i of
+// `min_mask` is set; thread i of the first NV writes it to out[i].
+template <int NV> __device__ __forceinline__ void block_reduce_store(const double (&v)[NV], unsigned min_mask, double *out) {
+  __shared__ double sh[RT_BLOCK / 64][NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const bool is_min = (min_mask >> i) & 1u;
+    double x = v[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const double y = __shfl_xor(x, o, 64);
+      x = is_min ? fmin(x, y) : x + y;
+    }
+    if (threadIdx.x % 64 == 0) sh[threadIdx.x / 64][i] = x;
+  }
   __syncthreads();
   if (threadIdx.x < NV) {
     const int i = threadIdx.x;
+    const bool is_min = (min_mask >> i) & 1u;
     double acc = sh[0][i];
-    for (int c = 1; c < CPB; ++c) acc = kind[i] ? fmin(acc, sh[c][i]) : acc + sh[c][i];
-    out_blk[i] = acc;
+    for (int w = 1; w < RT_BLOCK / 64; ++w) acc = is_min ? fmin(acc, sh[w][i]) : acc + sh[w][i];
+    out[i] = acc;
   }
 }
 
+// Conservation totals.  Bound by the one read of the intensities.  Every total is linear in
+// them, so a lane adds its own angles' terms V W I and V W I n over all its cells and the lanes
+// meet once, at the end of at most RT_DIAG_BLOCKS workgroups; four cells per lane are in
+// flight at a time, and the gas totals are a second, coalesced sweep.  With one reduction
+// per cell and one of ten values per 16 cells it took 198 us at 96^3 x 80 in FP32, now 80
+// (4.2 TB/s; the read alone is 61 us at the rate of a copy).
+#define RT_DIAG_BLOCKS 2048
+#define RT_DIAG_CELLS 4
 template <typename T, int LPC, int APL>
 __global__ __launch_bounds__(RT_BLOCK) void k_diag(int64_t N, int K, const double *dirs, const double *W,
                                                    double c_red, double c_light, const T *I, const double *vol,
-                                                   const double *etot, const double *mom, double *partial,
-                                                   int64_t nblk) {
-  const int64_t lb = rt_logical_block(nblk);
-  if (lb < 0) return;
-  constexpr int CPB = RT_BLOCK / LPC;
-  const int64_t cell = lb * CPB + threadIdx.x / LPC;
+                                                   const double *etot, const double *mom, double *partial) {
+  constexpr int CPB = RT_BLOCK / LPC, R = RT_DIAG_CELLS;
   const int l = threadIdx.x % LPC;
-  double v[ND] = {0, 0, 0, 0, 0, 0, 0, 0, INFINITY, 0};
-  const int kind[ND] = {0, 0, 0, 0, 0, 0, 0, 0, 1, 0};
-  if (cell < N) {
-    rt_lane_angles<double, LPC, APL> ang;
-    ang.load(dirs, W, K, l);
-    double E = 0, Fx = 0, Fy = 0, Fz = 0, mn = INFINITY, bad = 0;
-    for (int q = 0; q < APL; ++q) {
-      if (!ang.ok[q]) continue;
-      const double x = (double)I[cell * (int64_t)K + ang.k[q]];
-      if (!isfinite(x)) bad += 1;
-      mn = fmin(mn, x);
-      E += ang.w[q] * x;
-      Fx += ang.w[q] * ang.dx[q] * x;
-      Fy += ang.w[q] * ang.dy[q] * x;
-      Fz += ang.w[q] * ang.dz[q] * x;
+  rt_lane_angles<double, LPC, APL> ang;
+  ang.load(dirs, W, K, l);
+  double E = 0, Fx = 0, Fy = 0, Fz = 0, bad = 0;
+  T mn = (T)INFINITY;
+  for (int64_t c0 = (int64_t)blockIdx.x * (CPB * R); c0 < N; c0 += (int64_t)gridDim.x * (CPB * R)) {
+    T x[R][APL];
+    double V[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      // past the last cell: that cell again, with no volume
+      const int64_t c = c0 + r * CPB + threadIdx.x / LPC, cell = c < N ? c : N - 1;
+      V[r] = c < N ? vol[cell] : 0.0;
+#pragma unroll
+      for (int q = 0; q < APL; ++q) x[r][q] = I[cell * (int64_t)K + ang.k[q]];
     }
-    E = rt_group_sum<LPC>(E);
-    Fx = rt_group_sum<LPC>(Fx);
-    Fy = rt_group_sum<LPC>(Fy);
-    Fz = rt_group_sum<LPC>(Fz);
-    bad = rt_group_sum<LPC>(bad);
-    mn = rt_group_min<LPC>(mn);
-    const double V = vol[cell], fp = 4.0 * RT_PI;
-    const double eg = etot[cell];
-    const double m[3] = {mom[3 * cell], mom[3 * cell + 1], mom[3 * cell + 2]};
-    bad += !isfinite(eg) + !isfinite(m[0]) + !isfinite(m[1]) + !isfinite(m[2]);
-    v[0] = V * eg;
-    v[1] = V * (c_light / c_red) * fp * E;
-    v[2] = V * m[0];
-    v[3] = V * m[1];
-    v[4] = V * m[2];
-    v[5] = V * fp * Fx / c_red;
-    v[6] = V * fp * Fy / c_red;
-    v[7] = V * fp * Fz / c_red;
-    v[8] = mn;
-    v[9] = bad;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      double t = 0, tx = 0, ty = 0, tz = 0;
+#pragma unroll
+      for (int q = 0; q < APL; ++q) {
+        const double wx = ang.w[q] * (double)x[r][q];
+        t += wx;
+        tx += wx * ang.dx[q];
+        ty += wx * ang.dy[q];
+        tz += wx * ang.dz[q];
+        mn = fmin(mn, x[r][q]);
+      }
+      E += V[r] * t;
+      Fx += V[r] * tx;
+      Fy += V[r] * ty;
+      Fz += V[r] * tz;
+      // a non-finite intensity leaves t non-finite, whatever its weight
+      if (!isfinite(t) && c0 + r * CPB + threadIdx.x / LPC < N)
+        for (int q = 0; q < APL; ++q) bad += ang.ok[q] && !isfinite(x[r][q]);
+    }
   }
-  block_reduce_store<ND, LPC>(v, kind, partial + lb * ND);
+  double eg = 0, mx = 0, my = 0, mz = 0;
+  for (int64_t c = (int64_t)blockIdx.x * RT_BLOCK + threadIdx.x; c < N; c += (int64_t)gridDim.x * RT_BLOCK) {
+    const double V = vol[c], e = etot[c], m0 = mom[3 * c], m1 = mom[3 * c + 1], m2 = mom[3 * c + 2];
+    eg += V * e;
+    mx += V * m0;
+    my += V * m1;
+    mz += V * m2;
+    bad += !isfinite(e) + !isfinite(m0) + !isfinite(m1) + !isfinite(m2);
+  }
+  const double fp = 4.0 * RT_PI, f = fp / c_red;
+  const double v[ND] = {eg, (c_light / c_red) * fp * E, mx, my, mz, f * Fx, f * Fy, f * Fz, (double)mn, bad};
+  block_reduce_store<ND>(v, 1u << 8, partial + (int64_t)blockIdx.x * ND);
 }
 
-// Fold rows [blockIdx.x * chunk, +chunk) of an [nrows][nv] table into row blockIdx.x of
-// `out`: for column i, thread t folds rows t, t + 256, ... of the chunk in order, then a
-// fixed tree in LDS.  The chunking depends on nrows only, so results are deterministic.
-__global__ __launch_bounds__(RT_BLOCK) void k_fold(const double *partial, int64_t nrows, int nv,
-                                                   unsigned min_mask, int64_t chunk, double *out) {
-  __shared__ double sh[RT_BLOCK];
-  const int t = threadIdx.x;
+// Fold rows [blockIdx.x * chunk, +chunk) of an [nrows][NV] table into row blockIdx.x of
+// `out`: thread t folds rows t, t + 256, ... of the chunk in order, then the workgroup
+// reduction.  The chunking depends on nrows only, so results are deterministic.
+template <int NV>
+__global__ __launch_bounds__(RT_BLOCK) void k_fold(const double *partial, int64_t nrows, unsigned min_mask,
+                                                   int64_t chunk, double *out) {
   const int64_t r0 = (int64_t)blockIdx.x * chunk;
   const int64_t r1 = r0 + chunk < nrows ? r0 + chunk : nrows;
-  for (int i = 0; i < nv; ++i) {
-    const bool is_min = (min_mask >> i) & 1u;
-    double acc = is_min ? INFINITY : 0.0;
-    for (int64_t b = r0 + t; b < r1; b += RT_BLOCK) {
-      const double x = partial[b * nv + i];
-      acc = is_min ? fmin(acc, x) : acc + x;
+  double acc[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc[i] = (min_mask >> i) & 1u ? INFINITY : 0.0;
+  for (int64_t b = r0 + threadIdx.x; b < r1; b += RT_BLOCK)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const double x = partial[b * NV + i];
+      acc[i] = (min_mask >> i) & 1u ? fmin(acc[i], x) : acc[i] + x;
     }
-    sh[t] = acc;
-    __syncthreads();
-    for (int o = RT_BLOCK / 2; o > 0; o >>= 1) {
-      if (t < o) sh[t] = is_min ? fmin(sh[t], sh[t + o]) : sh[t] + sh[t + o];
-      __syncthreads();
-    }
-    if (t == 0) out[blockIdx.x * nv + i] = sh[0];
-    __syncthreads();
-  }
+  block_reduce_store<NV>(acc, min_mask, out + (int64_t)blockIdx.x * NV);
 }
 
-// Two folds: up to RT_BLOCK workgroups over contiguous chunks of the per-workgroup
-// partials into `mid` ([RT_BLOCK][nv]), then one workgroup over those into `out`.
-hipError_t reduce_partials(const double *partial, int64_t nrows, int nv, unsigned min_mask, double *mid,
-                           double *out, hipStream_t s) {
-  const int64_t g = nrows < RT_BLOCK ? nrows : RT_BLOCK;
-  const int64_t chunk = (nrows + g - 1) / g;
-  hipLaunchKernelGGL(k_fold, dim3((unsigned)g), dim3(RT_BLOCK), 0, s, partial, nrows, nv, min_mask, chunk, mid);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_fold, dim3(1), dim3(RT_BLOCK), 0, s, (const double *)mid, g, nv, min_mask, g, out);
+// One workgroup folds up to RT_FOLD_ROWS rows; more go through up to RT_BLOCK workgroups over
+// contiguous chunks into `mid` ([RT_BLOCK][NV]) first (13,824 rows of one value: 15 us in one
+// fold, 4.6 + 4.6 in two; 2048 rows of ten: 11 us in one).
+#define RT_FOLD_ROWS (8 * RT_BLOCK)
+template <int NV>
+hipError_t reduce_partials(const double *partial, int64_t nrows, unsigned min_mask, double *mid, double *out,
+                           hipStream_t s) {
+  if (nrows > RT_FOLD_ROWS) {
+    const int64_t chunk = (nrows + RT_BLOCK - 1) / RT_BLOCK;
+    const int64_t g = (nrows + chunk - 1) / chunk;
+    hipLaunchKernelGGL(k_fold<NV>, dim3((unsigned)g), dim3(RT_BLOCK), 0, s, partial, nrows, min_mask, chunk, mid);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    partial = mid;
+    nrows = g;
+  }
+  hipLaunchKernelGGL(k_fold<NV>, dim3(1), dim3(RT_BLOCK), 0, s, partial, nrows, min_mask, nrows, out);
   return hipGetLastError();
 }
 
 // Loss: each (face, angle) belongs to its upwind cell (A n_out . n_k > 0), which adds
 // u_f sigma 4 pi c W_k (A n_out . n_k) I to its partial loss and that coefficient to
 // its seed; sigma = -1 on a face's second cell since n_out = -n_f there.
+// A loss weights few faces (a plane's: 1% of the cells at 96^3), so what bounds it is finding
+// them.  A workgroup of RT_LOSS_CELLS consecutive cells first reads the weights of its
+// half-faces, one thread each (they are one contiguous range), marks the cells that have one
+// and ends there when none has.  The lanes of a marked cell then read one face each, with its
+// record, and take the weighted ones in face order.  With every lane of every cell reading
+// all its faces it took 400 us at 96^3 x 80 with the caches cold, now 80 (its 55 MB of
+// half-face ids and as much of weights: 24 us at the rate of a copy, 35 us without weights).
+#define RT_LOSS_CELLS 64
 template <typename T, int LPC, int APL>
 __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32_t *row_ptr, const int32_t *hf_face,
                                                    const double4 *hf_an, const double *dirs, const double *W,
@@ -134,39 +165,76 @@ __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32
   const int64_t lb = rt_logical_block(nblk);
   if (lb < 0) return;
   constexpr int CPB = RT_BLOCK / LPC;
-  const int64_t cell = lb * CPB + threadIdx.x / LPC;
-  const int l = threadIdx.x % LPC;
-  double v[1] = {0.0};
-  const int kind[1] = {0};
-  if (cell < N) {
-    rt_lane_angles<double, LPC, APL> ang;
-    ang.load(dirs, W, K, l);
-    const int64_t row = cell * (int64_t)K;
-    double sd[APL], Iv[APL];
-    for (int q = 0; q < APL; ++q) sd[q] = Iv[q] = 0.0;
-    bool have_row = false;  // the row is read only by cells with a weighted face (few)
-    const double fpc = 4.0 * RT_PI * c_light;
-    double part = 0.0;
-    const int h0 = row_ptr[cell], h1 = row_ptr[cell + 1];
-    constexpr int B = 4;  // faces whose ids and weights are fetched together
-    for (int hb = h0; hb < h1; hb += B) {
+  static_assert(RT_LOSS_CELLS == 64, "one bit per cell");
+  __shared__ int s_rows[RT_LOSS_CELLS + 1];
+  __shared__ unsigned long long s_mark;
+  const int64_t w0 = lb * RT_LOSS_CELLS;
+  const int nc = (int)(N - w0 < RT_LOSS_CELLS ? N - w0 : RT_LOSS_CELLS);
+  if (threadIdx.x <= nc) s_rows[threadIdx.x] = row_ptr[w0 + threadIdx.x];
+  if (threadIdx.x == 0) s_mark = 0;
+  __syncthreads();
+  {
+    const int h1 = s_rows[nc];
+    constexpr int B = 4;  // ids, then weights, fetched together
+    for (int hb = s_rows[0] + threadIdx.x; hb < h1; hb += B * RT_BLOCK) {
       int32_t fc[B];
       double u[B];
 #pragma unroll
-      for (int b = 0; b < B; ++b) fc[b] = hb + b < h1 ? hf_face[hb + b] : 0;
+      for (int b = 0; b < B; ++b) fc[b] = hf_face[hb + b * RT_BLOCK < h1 ? hb + b * RT_BLOCK : hb];
 #pragma unroll
-      for (int b = 0; b < B; ++b) u[b] = hb + b < h1 ? face_weight[fc[b] >= 0 ? fc[b] : -(int64_t)fc[b] - 1] : 0.0;
+      for (int b = 0; b < B; ++b) u[b] = face_weight[fc[b] >= 0 ? fc[b] : -(int64_t)fc[b] - 1];
 #pragma unroll
-      for (int b = 0; b < B; ++b) {
-        if (u[b] == 0.0) continue;
-        if (!have_row) {
-          for (int q = 0; q < APL; ++q) Iv[q] = ang.ok[q] ? (double)I[row + ang.k[q]] : 0.0;
-          have_row = true;
+      for (int b = 0; b < B; ++b)
+        if (u[b] != 0.0) {
+          const int h = hb + b * RT_BLOCK < h1 ? hb + b * RT_BLOCK : hb;
+          int c = 0, past = nc;  // rows[c] <= h < rows[past]
+          while (past - c > 1) {
+            const int mid = (c + past) / 2;
+            if (s_rows[mid] <= h) c = mid;
+            else past = mid;
+          }
+          atomicOr(&s_mark, 1ull << c);
         }
-        const double sg = fc[b] >= 0 ? u[b] : -u[b];
-        const double4 r = hf_an[hb + b];
+    }
+  }
+  __syncthreads();
+  const unsigned long long mark = s_mark;
+  if (mark == 0) {
+    if (threadIdx.x == 0) partial[lb] = 0.0;
+    return;
+  }
+  const int l = threadIdx.x % LPC;
+  rt_lane_angles<double, LPC, APL> ang;
+  ang.load(dirs, W, K, l);
+  const double fpc = 4.0 * RT_PI * c_light;
+  double part = 0.0;
+  const int marked = __popcll(mark);
+  for (int i = threadIdx.x / LPC; i < marked; i += CPB) {
+    unsigned long long m = mark;  // the i-th marked cell
+    for (int k = 0; k < i; ++k) m &= m - 1;
+    const int c = __ffsll(m) - 1;
+    const int64_t cell = w0 + c, row = cell * (int64_t)K;
+    double sd[APL], Iv[APL];
+    for (int q = 0; q < APL; ++q) sd[q] = Iv[q] = 0.0;
+    for (int q = 0; q < APL; ++q) Iv[q] = ang.ok[q] ? (double)I[row + ang.k[q]] : 0.0;
+    const int h1 = s_rows[c + 1];
+    for (int hb = s_rows[c]; hb < h1; hb += LPC) {
+      double u = 0.0;
+      double4 an = {0.0, 0.0, 0.0, 0.0};
+      if (hb + l < h1) {
+        const int32_t fc = hf_face[hb + l];
+        u = fc >= 0 ? face_weight[fc] : -face_weight[-(int64_t)fc - 1];
+        if (u != 0.0) an = hf_an[hb + l];
+      }
+      // the cell's weighted faces among these, in order
+      unsigned todo = (unsigned)(__ballot(u != 0.0) >> (threadIdx.x % 64 - l)) & ((1u << LPC) - 1u);
+      while (todo) {
+        const int b = __ffs(todo) - 1;
+        todo &= todo - 1;
+        const double sg = __shfl(u, b, LPC);
+        const double rx = __shfl(an.x, b, LPC), ry = __shfl(an.y, b, LPC), rz = __shfl(an.z, b, LPC);
         for (int q = 0; q < APL; ++q) {
-          const double m = r.x * ang.dx[q] + r.y * ang.dy[q] + r.z * ang.dz[q];
+          const double m = rx * ang.dx[q] + ry * ang.dy[q] + rz * ang.dz[q];
           if (m > 0.0) {
             const double coef = sg * fpc * ang.w[q] * m;
             part += coef * Iv[q];
@@ -178,9 +246,9 @@ __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32
     if (seed)
       for (int q = 0; q < APL; ++q)
         if (ang.ok[q] && sd[q] != 0.0) seed[row + ang.k[q]] = (T)((double)seed[row + ang.k[q]] + sd[q]);
-    v[0] = rt_group_sum<LPC>(part);
   }
-  block_reduce_store<1, LPC>(v, kind, partial + lb);
+  const double v[1] = {part};
+  block_reduce_store<1>(v, 0u, partial + lb);
 }
 
 // Angle moments of every cell (section 2.1): with intensities in energy-density units,
@@ -449,14 +517,14 @@ template <typename T, int LPC, int APL>
 hipError_t launch_diag(const rt_mesh *m, int K, const double *dirs, const double *W, double c_red, double c_light,
                        const void *I, const double *vol, const double *etot, const double *mom, double *out,
                        hipStream_t s) {
-  const int64_t cpb = RT_BLOCK / LPC;
-  const int64_t nblk = (m->N + cpb - 1) / cpb;
-  if (nblk > m->n_red_blocks) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_diag<T, LPC, APL>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK), 0, s, m->N, K, dirs,
-                     W, c_red, c_light, (const T *)I, vol, etot, mom, m->red, nblk);
+  constexpr int64_t cpb = RT_BLOCK / LPC * RT_DIAG_CELLS;
+  const int64_t all = (m->N + cpb - 1) / cpb, g = all < RT_DIAG_BLOCKS ? all : RT_DIAG_BLOCKS;
+  if (g > m->n_red_blocks) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_diag<T, LPC, APL>), dim3((unsigned)g), dim3(RT_BLOCK), 0, s, m->N, K, dirs, W, c_red, c_light,
+                     (const T *)I, vol, etot, mom, m->red);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return reduce_partials(m->red, nblk, ND, 1u << 8, m->red_mid, out, s);
+  return reduce_partials<ND>(m->red, g, 1u << 8, m->red_mid, out, s);
 }
 
 // The loss into `partial` (one row per workgroup, at most `cap` rows), folded through `mid`
@@ -465,15 +533,14 @@ template <typename T, int LPC, int APL>
 hipError_t launch_loss(const rt_mesh *m, int K, const double *dirs, const double *W, double c_light, const void *I,
                        const double *fw, double *loss, void *seed, double *partial, double *mid, int64_t cap,
                        hipStream_t s) {
-  const int64_t cpb = RT_BLOCK / LPC;
-  const int64_t nblk = (m->N + cpb - 1) / cpb;
+  const int64_t nblk = (m->N + RT_LOSS_CELLS - 1) / RT_LOSS_CELLS;
   if (nblk > cap) return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_loss<T, LPC, APL>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK), 0, s, m->N, K,
                      m->row_ptr, m->hf_face, m->hf_an64, dirs, W, c_light, (const T *)I, fw, (T *)seed, partial,
                      nblk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return reduce_partials(partial, nblk, 1, 0u, mid, loss, s);
+  return reduce_partials<1>(partial, nblk, 0u, mid, loss, s);
 }
 
 #define RT_DISPATCH(FN, T, ...)                                   \
@@ -591,7 +658,7 @@ hipError_t rt_launch_flux_loss(const rt_mesh *m, int K, const double *dirs, cons
 }
 
 int64_t rt_loss_blocks(int64_t N, int K) {
-  const int64_t cpb = (K % 16 == 0 || K > 64) ? RT_BLOCK / 16 : RT_BLOCK / 8;  // the lane layout of RT_DISPATCH
+  const int64_t cpb = (K % 16 == 0 || K > 64) ? RT_BLOCK / 16 : RT_BLOCK / 8;
   return (N + cpb - 1) / cpb;
 }
 

@@ -250,7 +250,9 @@ hipError_t rt_launch_flux_loss(const rt_mesh *m, int K, const double *dirs, cons
 // partial sums in a static device array of RT_NOALLOC_PARTIALS + RT_BLOCK doubles (2 MiB).
 #define RT_NOALLOC_PARTIALS ((1 << 18) - RT_BLOCK)
 #define RT_MAX_DEVICES 64
-int64_t rt_loss_blocks(int64_t N, int K);  // partial sums one loss launch writes
+// What the limit of the static array is held against: one partial sum per 16 or 32 cells (a
+// loss launch writes fewer, one per 64).
+int64_t rt_loss_blocks(int64_t N, int K);
 hipError_t rt_launch_flux_loss_noalloc(const rt_mesh *m, int K, const double *dirs, const double *W, double c_light,
                                        const void *I, const double *face_weight, double *loss, void *seed, int dtype,
                                        hipStream_t s);
