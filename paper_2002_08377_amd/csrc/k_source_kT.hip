@@ -21,24 +21,54 @@ struct kT_eval {
   double kP, kJ, S1, SG, SI, D, f, fp;
 };
 
-// Left to itself the compiler gives the larger paired instantiations all 256 registers plus
-// accumulation registers, one wave per SIMD; held to two waves the 10-angle ones spill 160
-// bytes per lane and still run faster (128^3 x 80: 3.09 -> 2.78 ms FP32, 3.20 -> 3.09 ms
-// FP64).  The other layouts keep the compiler's choice.
-template <int APL, int PAIRED> struct rt_kT_waves { static constexpr int value = PAIRED && APL <= 10 ? 2 : 1; };
-template <typename T, int LPC, int APL, bool FULL, int PAIRED>
-__global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_kT_waves<APL, PAIRED>::value))) void
+// x^b for b = half2 / 2 with a whole |half2| <= 40 (the same for every thread), x > 0, by
+// repeated squaring of x or its reciprocal: within |b| + 3 ulp.
+__device__ __forceinline__ double rt_half_power(double x, int half2) {
+  if (half2 < 0) x = rt_rcp(x);
+  unsigned m = half2 < 0 ? -half2 : half2;
+  double p = m & 1u ? sqrt(x) : 1.0;
+  for (m >>= 1; m; m >>= 1) {
+    if (m & 1u) p *= x;
+    x *= x;
+  }
+  return p;
+}
+
+// What bounds the kernel is FP64 vector issue: about five evaluations per cell, each over all
+// angles, so an evaluation is written for few instructions.  With u = y chi every sum is a
+// combination of the five sums over r'^2, r' = (1 + u) r:  with e = 1 / (1 + u),
+// 1 / r' = e + u e Gamma, so  sum Wt r = e (e P0 + u e P1),  sum Wt Gamma r = e (e P1 + u e P2)
+// and likewise for SI, and the chi-derivatives are -e^2 P1, -e^2 P2, -e^2 Q1: sums of positive
+// terms, no cancellation, and r' of order one keeps the squares in range for any u.  A power
+// law with a whole or half-whole exponent is a few multiplications instead of log and exp.
+// The directions and weights come from LDS (read by every lane before and after the
+// iteration).  64^3 x 80, exponent -3.5: 272 -> 175 us in FP32 (the sums and powers alone 240;
+// one evaluation fewer at either end of the iteration 187; three waves per SIMD the rest).
+// HALF: both exponents are whole or half-whole numbers (rt_half_power).
+//
+// Waves per SIMD the register use is held to: three where the spill stays within a few values
+// (10 angles per lane: 8), against 198 registers and two waves (351 -> 340 us for the step
+// above); log and exp take 30 registers more, and there three waves spill 50 (411 against 370).
+template <int APL, int PAIRED, bool HALF> struct rt_kT_waves {
+  static constexpr int value = HALF && (!PAIRED || APL <= 10) ? 3 : PAIRED && APL > 10 ? 1 : 2;
+};
+template <typename T, int LPC, int APL, bool FULL, int PAIRED, bool HALF>
+__global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_kT_waves<APL, PAIRED, HALF>::value))) void
 k_source_kT(rt_kT_args a, int64_t nblk) {
   using Ang = rt_step_angles<double, LPC, APL, FULL, PAIRED>;
   constexpr int CPB = RT_BLOCK / LPC;
+  __shared__ double s_dir[3 * RT_K_MAX], s_w[RT_K_MAX];
   const int64_t lb = rt_logical_block(nblk);
-  if (lb < 0) return;
+  if (lb < 0) return;  // whole workgroup
+  const int K = a.K;
+  for (int i = threadIdx.x; i < 3 * K; i += RT_BLOCK) s_dir[i] = a.dirs[i];
+  for (int i = threadIdx.x; i < K; i += RT_BLOCK) s_w[i] = a.W[i];
+  __syncthreads();
   const int64_t cell = lb * CPB + threadIdx.x / LPC;
   if (cell >= a.N) return;
   const int l = threadIdx.x % LPC;
-  const int K = a.K;
   Ang ang;
-  ang.load(a.dirs, a.W, K, l);
+  ang.load(s_dir, s_w, K, l);
   T *Ir = (T *)a.I + cell * (int64_t)K;
 
   const double rho = a.rho[cell];
@@ -49,23 +79,25 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
   const double irho = rt_rcp(rho), ic = rt_rcp(c);
   const double vx = m0 * irho, vy = m1 * irho, vz = m2 * irho;
   const double gam = rsqrt(1.0 - (vx * vx + vy * vy + vz * vz) * (ic * ic));
-  double Gm[APL], Wt[APL], Ic[APL];
+  double Gm[APL], Wt[APL], WI[APL];  // Gamma, W~ and W~ I~
   double norm = 0.0;
 #pragma unroll
   for (int q = 0; q < APL; ++q) {
     const double I0 = (double)Ir[ang.k[q]];
     const double vn = vx * ang.dx(q) + vy * ang.dy(q) + vz * ang.dz(q);
     Gm[q] = gam * (1.0 - vn * ic);
-    const double G2 = Gm[q] * Gm[q];
     const double iG = rt_rcp(Gm[q]);
-    Ic[q] = G2 * G2 * I0;
     Wt[q] = ang.wt(q) * (iG * iG);
+    WI[q] = ang.wt(q) * (Gm[q] * Gm[q]) * I0;  // W Gamma^-2 Gamma^4 I
     norm += Wt[q];
   }
   norm = rt_group_sum<LPC>(norm);
   const double inorm = rt_rcp(norm);
 #pragma unroll
-  for (int q = 0; q < APL; ++q) Wt[q] *= inorm;
+  for (int q = 0; q < APL; ++q) {
+    Wt[q] *= inorm;
+    WI[q] *= inorm;
+  }
   const double y = a.dt * a.c_red * rho;
   const double rcv = rho * a.cv;
   const double Tn = (Eg - 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) * irho) * rt_rcp(rcv);
@@ -74,39 +106,52 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
 
   auto evaluate = [&](double Tq) {
     kT_eval e;
-    // (T/T_ref)^b as exp(b ln(T/T_ref)): within (|b ln(T/T_ref)| + 2) ulp, and far cheaper
-    // than pow (whose code alone, even on a branch not taken, costs this kernel registers).
-    // The error stays below the Newton stopping tolerance (1e-14 T) while |b ln| < ~40;
-    // beyond that the bracketed iteration still ends, through its bisection steps.
-    const double lt = log(Tq * iTref);
-    const double pP = exp(a.bP * lt);
+    const double x = Tq * iTref;
+    double pP, pJ;
+    if constexpr (HALF) {
+      pP = rt_half_power(x, a.bP2);
+      pJ = a.bJ2 == a.bP2 ? pP : rt_half_power(x, a.bJ2);
+    } else {
+      // (T/T_ref)^b as exp(b ln(T/T_ref)): within (|b ln(T/T_ref)| + 2) ulp, and far cheaper
+      // than pow (whose code alone, even on a branch not taken, costs this kernel registers).
+      // The error stays below the Newton stopping tolerance (1e-14 T) while |b ln| < ~40;
+      // beyond that the bracketed iteration still ends, through its bisection steps.
+      const double lt = log(x);
+      pP = exp(a.bP * lt);
+      pJ = a.bJ == a.bP ? pP : exp(a.bJ * lt);
+    }
     e.kP = kP0 * pP;
-    e.kJ = kJ0 * (a.bJ == a.bP ? pP : exp(a.bJ * lt));
-    const double chi = e.kJ + ks;
-    double s1 = 0, sG = 0, sI = 0, p1 = 0, pG = 0, pI = 0;
+    e.kJ = kJ0 * pJ;
+    const double u = y * (e.kJ + ks);
+    const double ie = rt_rcp(1.0 + u), ue = u * ie;
+    double P0 = 0, P1 = 0, P2 = 0, Q0 = 0, Q1 = 0;
 #pragma unroll
     for (int q = 0; q < APL; ++q) {
-      const double r = rt_rcp(1.0 + y * chi * Gm[q]);
-      s1 += Wt[q] * r;
-      sG += Wt[q] * Gm[q] * r;
-      sI += Wt[q] * Ic[q] * r;
-      p1 += Wt[q] * Gm[q] * r * r;
-      pG += Wt[q] * Gm[q] * Gm[q] * r * r;
-      pI += Wt[q] * Ic[q] * Gm[q] * r * r;
+      const double r = rt_rcp(fma(ue, Gm[q], ie));
+      const double r2 = r * r;
+      const double w = Wt[q] * r2, wG = w * Gm[q], wI = WI[q] * r2;
+      P0 += w;
+      P1 += wG;
+      P2 = fma(wG, Gm[q], P2);
+      Q0 += wI;
+      Q1 = fma(wI, Gm[q], Q1);
     }
-    e.S1 = rt_group_sum<LPC>(s1);
-    e.SG = rt_group_sum<LPC>(sG);
-    e.SI = rt_group_sum<LPC>(sI);
-    p1 = rt_group_sum<LPC>(p1);
-    pG = rt_group_sum<LPC>(pG);
-    pI = rt_group_sum<LPC>(pI);
+    P0 = rt_group_sum<LPC>(P0);
+    P1 = rt_group_sum<LPC>(P1);
+    P2 = rt_group_sum<LPC>(P2);
+    Q0 = rt_group_sum<LPC>(Q0);
+    Q1 = rt_group_sum<LPC>(Q1);
+    e.S1 = ie * fma(ue, P1, ie * P0);
+    e.SG = ie * fma(ue, P2, ie * P1);
+    e.SI = ie * fma(ue, Q1, ie * Q0);
     e.D = e.S1 + y * e.kJ * e.SG;
     const double T3 = Tq * Tq * Tq, T4 = T3 * Tq;
     const double Nn = e.kP * a.a_rad * T4 * e.S1 - fourpi * e.kJ * e.SI;
     const double iD = rt_rcp(e.D), iTq = rt_rcp(Tq);
     e.f = rcv * (Tq - Tn) + a.dt * c * rho * Nn * iD;
     const double dkP = a.bP * e.kP * iTq, dkJ = a.bJ * e.kJ * iTq;
-    const double dS1 = -y * p1 * dkJ, dSG = -y * pG * dkJ, dSI = -y * pI * dkJ;
+    const double dr = -y * dkJ * (ie * ie);
+    const double dS1 = dr * P1, dSG = dr * P2, dSI = dr * Q1;
     const double dD = dS1 + y * (dkJ * e.SG + e.kJ * dSG);
     const double dN = dkP * a.a_rad * T4 * e.S1 + e.kP * a.a_rad * 4.0 * T3 * e.S1 + e.kP * a.a_rad * T4 * dS1 -
                       fourpi * (dkJ * e.SI + e.kJ * dSI);
@@ -114,71 +159,79 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
     return e;
   };
 
-  // Bracket the root from T^n, then safeguarded Newton inside the bracket.  One loop with a
-  // single evaluation site (mode 0: at T^n; 1: doubling hi while f < 0; 2: halving lo while
-  // f > 0; 3: Newton), taking the same steps in the same order as the two bracket loops and
-  // the Newton loop it replaces, so the kernel holds one copy of the evaluation.
-  double Tq = Tn, lo = Tn, hi = Tn, x = Tn;
-  int mode = 0;
-  bool done = false;
+  // Safeguarded Newton from T^n, one loop with a single evaluation site.  The bracket's far end
+  // is the first of 2 T^n, 4 T^n, ... with f >= 0 (f(T^n) < 0; else of T^n / 2, ... with f <= 0),
+  // but it is only looked for (modes 1 and 2) once a step would leave the first interval
+  // (`open`): steps that stay inside it are the same whatever the far end is, and its
+  // evaluation is one of about six.  A step is the last when it is at most 1e-14 T, or when
+  // quadratic convergence (the next step is about step^3 / previous^2, both of them Newton
+  // steps) puts the one after it below the rounding of T, which would only confirm it.
+  // The search for the far end keeps nothing of the evaluation at the current T: it is done
+  // again there when the end is found (held through the loop it cost a fifth of the registers).
+  double Tq = Tn, lo = Tn, hi = Tn, x = Tn, prev = 0.0;
+  int mode = 0;  // 0: at T^n; 1: doubling hi; 2: halving lo; 3: Newton
+  bool open = false, up = false, done = false;
   kT_eval e;
   for (int nev = 1;; ++nev) {
-    const kT_eval r = evaluate(x);
+    e = evaluate(x);
+    const bool neg = e.f < 0.0, pos = e.f > 0.0;
+    if (mode == 1 || mode == 2) {
+      const bool on = nev < 200 && (up ? neg : pos);
+      hi = up && on ? 2.0 * hi : hi;
+      lo = !up && on ? 0.5 * lo : lo;
+      mode = on ? mode : 3;
+      done = nev >= 200;
+      x = !on ? Tq : up ? hi : lo;
+      continue;
+    }
+    Tq = x;
+    if (done || nev >= 200 || e.f == 0.0) break;
     if (mode == 0) {
-      e = r;
-      mode = r.f < 0.0 ? 1 : r.f > 0.0 ? 2 : 3;
-    } else if (mode == 1) {
-      if (!(r.f < 0.0)) mode = 3;
-    } else if (mode == 2) {
-      if (!(r.f > 0.0)) mode = 3;
-    } else {
-      Tq = x;
-      e = r;
-      if (done) break;
+      mode = 3;
+      up = neg;
+      open = neg || pos;
+      hi = neg ? 2.0 * Tn : hi;
+      lo = pos ? 0.5 * Tn : lo;
     }
-    if (nev >= 200) break;
-    if (mode == 1) {
-      lo = hi;
-      hi *= 2.0;
-      x = hi;
-      continue;
-    }
-    if (mode == 2) {
-      hi = lo;
-      lo *= 0.5;
-      x = lo;
-      continue;
-    }
-    if (e.f == 0.0) break;
-    if (e.f < 0.0) lo = Tq;
-    else hi = Tq;
+    lo = neg ? Tq : lo;
+    hi = neg ? hi : Tq;
+    open = open && up == neg;
     double Tx = Tq - e.f * rt_rcp(e.fp);
+    const double step = fabs(Tx - Tq);
+    const bool in = Tx > lo && Tx < hi;
     // a step within the tolerance has converged and is taken as it is; a larger one that
     // leaves the bracket is replaced by bisection
-    done = fabs(Tx - Tq) <= 1e-14 * Tq;
-    if (!done && !(Tx > lo && Tx < hi)) Tx = 0.5 * (lo + hi);
-    x = Tx;
+    done = step <= 1e-14 * Tq;
+    if (!done && !in && open) {
+      open = false;
+      mode = up ? 1 : 2;
+      x = up ? hi : lo;
+      continue;
+    }
+    x = done || in ? Tx : 0.5 * (lo + hi);
+    done = done || (in && step * step * step <= 2e-16 * Tq * (prev * prev));
+    prev = in ? step : 0.0;
   }
 
   // The directions and weights are needed before the iteration and after it, not in it: read
-  // them again here (through a pointer the compiler cannot prove unchanged, so it does not keep
+  // them again here (through an offset the compiler cannot prove zero, so it does not keep
   // the first copy live through the iteration) instead of holding them in registers.
-  const double *dirs_again = a.dirs, *W_again = a.W;
-  asm volatile("" : "+s"(dirs_again), "+s"(W_again));
-  ang.load(dirs_again, W_again, K, l);
+  int again = 0;
+  asm volatile("" : "+s"(again));
+  ang.load(s_dir + again, s_w + again, K, l);
   const double T4 = Tq * Tq * Tq * Tq;
   const double planck = a.a_rad * T4 * (1.0 / fourpi);
   const double Jc = (e.SI + y * e.kP * e.SG * planck) * rt_rcp(e.D);
-  const double chi = e.kJ + ks;
+  const double yS = y * (e.kP * planck + ks * Jc), yc = y * (e.kJ + ks);
   double dE = 0, dFx = 0, dFy = 0, dFz = 0;
 #pragma unroll
   for (int q = 0; q < APL; ++q) {
-    const double Inew = (Ic[q] + y * Gm[q] * (e.kP * planck + ks * Jc)) * rt_rcp(1.0 + y * chi * Gm[q]);
+    // I' = (Gamma^4 I + y Gamma S) r / Gamma^4 = r (I + y S / Gamma^3), the incoming value
+    // read again rather than held through the iteration
+    const double I0 = (double)Ir[ang.k[q]];
     const double iG = rt_rcp(Gm[q]);
-    const double iG2 = iG * iG;
-    const T out = (T)(Inew * (iG2 * iG2));
-    // the incoming value is read again here rather than held through the iteration
-    const double wd = ang.wt(q) * ((double)Ir[ang.k[q]] - (double)out);
+    const T out = (T)((I0 + yS * (iG * iG * iG)) * rt_rcp(1.0 + yc * Gm[q]));
+    const double wd = ang.wt(q) * (I0 - (double)out);
     if (ang.ok[q]) Ir[ang.k[q]] = out;
     dE += wd;
     dFx += wd * ang.dx(q);
@@ -199,11 +252,16 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
 }
 
 template <typename T, int LPC, int APL, bool FULL, int PAIRED>
-hipError_t launch(const rt_kT_args &a, hipStream_t s) {
+hipError_t launch(const rt_kT_args &args, hipStream_t s) {
+  rt_kT_args a = args;
+  a.bP2 = (int)(2.0 * a.bP);
+  a.bJ2 = (int)(2.0 * a.bJ);
+  const bool half = a.bP2 == 2.0 * a.bP && a.bJ2 == 2.0 * a.bJ;
   const int64_t cpb = RT_BLOCK / LPC;
   const int64_t nblk = (a.N + cpb - 1) / cpb;
-  hipLaunchKernelGGL((k_source_kT<T, LPC, APL, FULL, PAIRED>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK),
-                     0, s, a, nblk);
+  const dim3 grid((unsigned)rt_grid_for(nblk)), block(RT_BLOCK);
+  if (half) hipLaunchKernelGGL((k_source_kT<T, LPC, APL, FULL, PAIRED, true>), grid, block, 0, s, a, nblk);
+  else hipLaunchKernelGGL((k_source_kT<T, LPC, APL, FULL, PAIRED, false>), grid, block, 0, s, a, nblk);
   return hipGetLastError();
 }
 

@@ -208,6 +208,7 @@ struct rt_kT_args {
   const double *kP0, *kJ0, *ks;
   double *T_out;
   double T_ref, bP, bJ;
+  int bP2, bJ2;  // 2 bP, 2 bJ where those are whole numbers (set at dispatch)
   double c_red, c_light, a_rad, cv, dt;
   double e_gain, m_gain;
   int paired;  // rt_pair_kind of the angle layout
