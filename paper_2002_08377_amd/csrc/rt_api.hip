@@ -9,6 +9,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <exception>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -40,19 +41,43 @@ int hip_fail(hipError_t e, const char *what) {
     if (e_ != hipSuccess) return hip_fail(e_, what); \
   } while (0)
 
+// Device arrays that live and die together, cut from one allocation (each 256-byte aligned):
+// an upload and its release made and freed some thirty of them, 1.6 ms at 64,000 cells
+// against 0.5.
+class rt_arena {
+ public:
+  template <typename P> void add(P *&p, size_t bytes) {
+    p = nullptr;
+    if (bytes == 0) return;
+    items_[n_++] = {(void **)&p, total_};
+    total_ += (bytes + 255) / 256 * 256;
+  }
+  hipError_t allocate(void **base) {
+    *base = nullptr;
+    if (total_ == 0) return hipSuccess;
+    const hipError_t e = hipMalloc(base, total_);
+    if (e != hipSuccess) {
+      *base = nullptr;
+      return e;
+    }
+    for (int i = 0; i < n_; ++i) *items_[i].p = (char *)*base + items_[i].at;
+    return hipSuccess;
+  }
+
+ private:
+  struct item {
+    void **p;
+    size_t at;
+  };
+  item items_[32];  // more than an upload has
+  int n_ = 0;
+  size_t total_ = 0;
+};
+
 template <typename P> hipError_t dmalloc(P **p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) return hipSuccess;
   return hipMalloc((void **)p, bytes);
-}
-
-void free_mesh_arrays(rt_mesh *m) {
-  void *ptrs[] = {m->vol0,     m->D,       m->wn,      m->row_ptr,    m->hf_nbr,     m->hf_face,
-                  m->hf_an64,   m->hf_an32, m->hf_gp64, m->hf_rel64,   m->hf_gp32,    m->hf_rel32,
-                  m->gb64,      m->gb32,    m->I_half,  m->grad,       m->lam_star,   m->red,
-                  m->red_mid,   m->wg_order16, m->wg_order32, m->wg_order64};
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
 }
 
 bool aligned8(const void *p) { return ((uintptr_t)p & 7u) == 0; }
@@ -301,23 +326,17 @@ int rt_mesh_upload(rt_mesh **out, int64_t N, int64_t F, int32_t k_max, int32_t f
       !face_centroid)
     return fail(RT_EINVAL, "a mesh array is NULL");
   if (!(box > 0.0) || !isfinite(box)) return fail(RT_EINVAL, "box must be positive");
-  {
+  rt_host_mesh hm;
+  try {
     // positions, centres of mass, velocities and centroids enter the face speeds and the
     // reconstruction offsets: a non-finite entry would give non-finite intensities later
-    const struct {
-      const double *p;
-      int64_t n;
-      const char *what;
-    } arrs[] = {{gen, 3 * N, "gen_pos"}, {com, 3 * N, "com"}, {mesh_vel, 3 * N, "mesh_vel"},
-                {face_centroid, 3 * F, "face_centroid"}};
-    for (const auto &a : arrs)
-      for (int64_t k = 0; k < a.n; ++k)
-        if (!isfinite(a.p[k])) return fail(RT_EINVAL, "%s has a non-finite entry (index %lld)", a.what, (long long)k);
-  }
-  rt_host_mesh hm;
-  {
-    const std::string why = rt_build_host_mesh(N, F, vol, face_cells, face_shift, face_area, face_normal, hm);
+    const rt_finite_check finite[] = {{gen, 3 * N, "gen_pos"}, {com, 3 * N, "com"}, {mesh_vel, 3 * N, "mesh_vel"},
+                                      {face_centroid, 3 * F, "face_centroid"}};
+    const std::string why =
+        rt_build_host_mesh(N, F, vol, face_cells, face_shift, face_area, face_normal, hm, finite, 4);
     if (!why.empty()) return fail(RT_EINVAL, "%s", why.c_str());
+  } catch (const std::exception &x) {
+    return fail(RT_ENOMEM, "host memory for the half-face index: %s", x.what());
   }
   const int64_t H = 2 * F;
   const std::vector<int32_t> &row_ptr = hm.row_ptr;
@@ -359,11 +378,8 @@ int rt_mesh_upload(rt_mesh **out, int64_t N, int64_t F, int32_t k_max, int32_t f
   const bool plm = flags & RT_MESH_PLM;
   const int64_t nred = (N + 7) / 8 + 8;  // >= blocks of any cell-parallel kernel (>= 8 cells per block)
   m->n_red_blocks = nred;
-  hipError_t e = hipSuccess;
-#define RT_ALLOC(ptr, bytes)                         \
-  do {                                               \
-    if (e == hipSuccess) e = dmalloc(&(ptr), bytes); \
-  } while (0)
+  rt_arena kept;
+#define RT_ALLOC(ptr, bytes) kept.add(ptr, bytes)
   RT_ALLOC(m->vol0, sizeof(double) * N);
   RT_ALLOC(m->D, sizeof(double) * N);
   RT_ALLOC(m->wn, sizeof(double) * F);
@@ -388,27 +404,25 @@ int rt_mesh_upload(rt_mesh **out, int64_t N, int64_t F, int32_t k_max, int32_t f
   RT_ALLOC(m->wg_order16, N);
   RT_ALLOC(m->wg_order32, N);
   RT_ALLOC(m->wg_order64, N);
+#undef RT_ALLOC
   // temporaries of the upload
   double *d_gen = nullptr, *d_com = nullptr, *d_w = nullptr, *d_area = nullptr, *d_nrm = nullptr, *d_cen = nullptr;
   int32_t *d_fc = nullptr;
   int8_t *d_shift = nullptr;
-  RT_ALLOC(d_gen, sizeof(double) * 3 * N);
-  RT_ALLOC(d_com, sizeof(double) * 3 * N);
-  RT_ALLOC(d_w, sizeof(double) * 3 * N);
-  RT_ALLOC(d_area, sizeof(double) * F);
-  RT_ALLOC(d_nrm, sizeof(double) * 3 * F);
-  RT_ALLOC(d_cen, sizeof(double) * 3 * F);
-  RT_ALLOC(d_fc, sizeof(int32_t) * 2 * F);
-  RT_ALLOC(d_shift, 3 * F);
-#undef RT_ALLOC
-  auto cleanup_tmp = [&]() {
-    void *t[] = {d_gen, d_com, d_w, d_area, d_nrm, d_cen, d_fc, d_shift};
-    for (void *p : t)
-      if (p) (void)hipFree(p);
-  };
+  rt_arena upload;
+  upload.add(d_gen, sizeof(double) * 3 * N);
+  upload.add(d_com, sizeof(double) * 3 * N);
+  upload.add(d_w, sizeof(double) * 3 * N);
+  upload.add(d_area, sizeof(double) * F);
+  upload.add(d_nrm, sizeof(double) * 3 * F);
+  upload.add(d_cen, sizeof(double) * 3 * F);
+  upload.add(d_fc, sizeof(int32_t) * 2 * F);
+  upload.add(d_shift, 3 * F);
+  void *tmp = nullptr;
+  hipError_t e = kept.allocate(&m->arena);
+  if (e == hipSuccess) e = upload.allocate(&tmp);
   if (e != hipSuccess) {
-    cleanup_tmp();
-    free_mesh_arrays(m);
+    if (m->arena) (void)hipFree(m->arena);
     delete m;
     return fail(RT_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
   }
@@ -434,9 +448,9 @@ int rt_mesh_upload(rt_mesh **out, int64_t N, int64_t F, int32_t k_max, int32_t f
   if (e == hipSuccess && plm) e = rt_launch_gradient_base(m, d_fc, d_area, d_cen, d_gen, d_shift, st);
   if (e == hipSuccess) e = rt_launch_volume_rate(m, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  cleanup_tmp();
+  (void)hipFree(tmp);
   if (e != hipSuccess) {
-    free_mesh_arrays(m);
+    (void)hipFree(m->arena);
     delete m;
     return hip_fail(e, "mesh upload");
   }
@@ -447,7 +461,7 @@ int rt_mesh_upload(rt_mesh **out, int64_t N, int64_t F, int32_t k_max, int32_t f
 int rt_mesh_free(rt_mesh *m) {
   if (!m) return RT_OK;
   (void)hipDeviceSynchronize();
-  free_mesh_arrays(m);
+  (void)hipFree(m->arena);
   delete m;
   return RT_OK;
 }

@@ -14,6 +14,7 @@ struct rt_mesh {
   int64_t N, F, H;  // cells, faces, half-faces (= 2F)
   int32_t k_max, flags;
   double box;
+  void *arena;        // the one allocation every device array below is cut from
   // geometry resident on the device
   double *vol0;       // [N] geometric volumes (gradient estimator)
   double *D;          // [N] volume rate sum_faces A (w~.n), outward positive
