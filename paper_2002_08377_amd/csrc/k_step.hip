@@ -33,9 +33,10 @@ template <typename T, int PAIRED> struct rt_batch {
 // Occupancy target: the FP64 PLM stage 2 (four rows gathered per face) would take all 256
 // registers at one wave per SIMD; held to two it spills ~130 bytes per lane and runs 5%
 // faster with antipodes K/2 apart (64^3 x 80 PLM step 1.96 -> 1.87 ms; unchanged with them
-// side by side).  Everything else keeps the compiler's choice.
+// side by side).  The FP64 source reverse would take 262 registers, again one wave: held to
+// two it spills five of them.  Everything else keeps the compiler's choice.
 template <typename T, int MODE> struct rt_step_waves {
-  static constexpr int value = MODE == 2 && sizeof(T) == 8 ? 2 : 1;
+  static constexpr int value = sizeof(T) == 8 && (MODE == 2 || MODE >= 4) ? 2 : 1;
 };
 template <typename T, int LPC, int APL, int MODE, bool FULL, int PAIRED>
 __global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_step_waves<T, MODE>::value))) void
