@@ -21,15 +21,19 @@ namespace {
 // are staged in LDS once and every lane group reads them from there.  Neighbour rows
 // are gathered two faces per batch, all loads of a batch issued before any is used.
 // Output: the limited gradient as [N][3][K] (PACKED false), or, for the PLM step's own
-// stage 2, each cell and angle's (phi, alpha grad phi) as one 4-vector, [N][K][4]
-// (PACKED true), so stage 2 gathers a neighbour's face state with one access per angle.
-template <typename T, int LPC, int APL, bool PACKED>
+// stage 2, each cell and angle's face state (phi, alpha grad phi) in 16-byte parts (PACKED
+// true).  Bound by the address units of its gathers (FP64 64^3 x 80: 0.29 of 0.39 ms) and the
+// bytes of its output; in a full layout (K = LPC APL) a neighbour's elements sit at compile-time
+// offsets from one 64-bit multiply-add per face (two PLM steps at 64^3 x 80, FP64 2.63 -> 2.54
+// ms).  Two or four consecutive angles per lane (fewer, wider gathers) spread its stores over
+// more lines: FP64 2.59 ms with two, FP32 1.34 -> 1.42 with two and 1.79 with four.
+template <typename T, int LPC, int APL, bool FULL, bool PACKED>
 __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const int32_t *__restrict__ row_ptr,
                                                        const int32_t *__restrict__ hf_nbr, const void *hf_gp,
                                                        const void *hf_rel, const void *cell_gb,
                                                        const double *__restrict__ vol0,
                                                        const T *__restrict__ I, T *__restrict__ G, int hf_cap,
-                                                       int64_t nblk) {
+                                                       int64_t nblk, bool past_caches) {
   using V4 = typename rt_vec4<T>::type;
   constexpr int U = 2;
   constexpr int CPB = RT_BLOCK / LPC;
@@ -64,7 +68,7 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
 #pragma unroll
   for (int q = 0; q < APL; ++q) {
     const int k = l + LPC * q;
-    ok[q] = k < K;
+    ok[q] = FULL || k < K;
     kk[q] = ok[q] ? k : 0;
     s[q] = I[row + kk[q]];
     gx[q] = s[q] * b.x;
@@ -76,21 +80,23 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
   for (int h = h0; h < h1; h += U) {
     // slots past the cell's last face repeat its first face with zero weights; they
     // leave the sums unchanged and re-read a neighbour already in the min/max
-    int64_t j[U];
+    uint32_t j[U];
     V4 e[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool v = h + u < h1;
       const int i = (v ? h + u : h0) - H0;
-      j[u] = s_nbr[i];
+      j[u] = (uint32_t)s_nbr[i];
       e[u] = s_gp[i];
       if (!v) e[u] = V4{T(0), T(0), T(0), T(0)};
     }
     T o[U][APL];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      const T *n = (const T *)((const char *)I + (uint64_t)j[u] * (uint32_t)(K * sizeof(T)));
 #pragma unroll
-      for (int q = 0; q < APL; ++q) o[u][q] = I[j[u] * K + kk[q]];
+      for (int q = 0; q < APL; ++q) o[u][q] = FULL ? (n + l)[LPC * q] : n[kk[q]];
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -128,8 +134,10 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
     if (dmin[q] < T(0)) al = fmin(al, (lo[q] - s[q]) * rt_rcp_refined(dmin[q]));
     const int k = kk[q];
     if constexpr (PACKED) {
-      using V4 = typename rt_vec4<T>::type;
-      ((V4 *)G)[cell * K + k] = V4{s[q], al * gx[q], al * gy[q], al * gz[q]};
+      using S = rt_state<T>;
+      typename S::part *o = (typename S::part *)G + S::PARTS * cell * K + k;
+      if (FULL && past_caches) S::template store<true>(o, K, s[q], al * gx[q], al * gy[q], al * gz[q]);
+      else S::template store<false>(o, K, s[q], al * gx[q], al * gy[q], al * gz[q]);
     } else {
       G[(cell * 3 + 0) * K + k] = al * gx[q];
       G[(cell * 3 + 1) * K + k] = al * gy[q];
@@ -138,8 +146,8 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
   }
 }
 
-template <typename T, int LPC, int APL, bool PACKED>
-hipError_t launch(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s) {
+template <typename T, int LPC, int APL, bool FULL, bool PACKED>
+hipError_t launch_one(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s) {
   using V4 = typename rt_vec4<T>::type;
   const int64_t cpb = RT_BLOCK / LPC;
   const int64_t nblk = (m->N + cpb - 1) / cpb;
@@ -149,9 +157,21 @@ hipError_t launch(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s
   const int cap = cpb == 16 ? m->hf_cap16 : m->hf_cap32;
   const size_t smem = (2 * sizeof(V4) + sizeof(int32_t)) * (size_t)cap;
   if (smem > (size_t)m->lds_max) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((k_gradient<T, LPC, APL, PACKED>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK), smem, s,
-                     m->N, K, m->row_ptr, m->hf_nbr, gp, rel, gb, m->vol0, (const T *)I, (T *)G, cap, nblk);
+  // States that outgrow the 256 MB Infinity Cache (with half of it for the rest of the step)
+  // are stored past the caches, to leave those to the gathered rows: 335 MB (FP32, 64^3 x 80)
+  // 1.38 -> 1.36 ms per two PLM steps and 671 MB (FP64) 2.67 -> 2.63 ms; smaller ones are read
+  // back from that cache: 85 MB (FP32, 48^3 x 48) 0.44 ms past the caches, 0.42 ms through them.
+  const bool past_caches = PACKED && (int64_t)sizeof(V4) * m->N * K > (int64_t)128 << 20;
+  hipLaunchKernelGGL((k_gradient<T, LPC, APL, FULL, PACKED>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK), smem,
+                     s, m->N, K, m->row_ptr, m->hf_nbr, gp, rel, gb, m->vol0, (const T *)I, (T *)G, cap, nblk,
+                     past_caches);
   return hipGetLastError();
+}
+
+template <typename T, int LPC, int APL, bool PACKED>
+hipError_t launch(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s) {
+  return K == LPC * APL ? launch_one<T, LPC, APL, true, PACKED>(m, K, I, G, s)
+                        : launch_one<T, LPC, APL, false, PACKED>(m, K, I, G, s);
 }
 
 template <typename T, bool PACKED>

@@ -13,8 +13,14 @@ namespace {
 // faster than four in FP32.  The FP64 form with antipodes side by side ran 5% faster with
 // three (1.91 against 2.00 ms) at two waves per SIMD; since its source holds fewer values
 // (three waves) two are faster again: 1.85 ms, against 2.45 ms with three.
-template <typename T, int PAIRED> struct rt_batch {
+// PLM stage 2 holds four values per gathered state, and of a pair gathers one: one face at a
+// time at 8 to 12 angles per lane (two cost a wave per SIMD: 64^3 x 80 step, FP32 0.69 against
+// 0.70 ms, FP64 1.34 against 1.72), two at 4 and 6 (one: 48^3 x 24, FP32 0.138 against 0.142),
+// four at 2 (two: 40^3 x 8, FP32 0.062 against 0.064 ms); without pairs two (one: 48^3 x 37,
+// FP32 0.196 against 0.202 ms, FP64 0.37 against 0.48).
+template <typename T, int APL, int PAIRED> struct rt_batch {
   static constexpr int U = 2;
+  static constexpr int PLM = !PAIRED ? 2 : APL > 6 ? 1 : APL > 2 ? 2 : 4;
 };
 
 // MODE 0: source only (in place); 1: upwind transport (+ source); 2: reconstructed
@@ -30,11 +36,9 @@ template <typename T, int PAIRED> struct rt_batch {
 // The cells of a workgroup are consecutive, so their half-faces form one contiguous
 // range; it is staged in LDS (dynamic size: the largest range of any workgroup,
 // found at upload) and the face loops read their records from there.
-// Occupancy target: the FP64 PLM stage 2 (four rows gathered per face) would take all 256
-// registers at one wave per SIMD; held to two it spills ~130 bytes per lane and runs 5%
-// faster with antipodes K/2 apart (64^3 x 80 PLM step 1.96 -> 1.87 ms; unchanged with them
-// side by side).  The FP64 source reverse would take 262 registers, again one wave: held to
-// two it spills five of them.  Everything else keeps the compiler's choice.
+// Occupancy target: the FP64 PLM stage 2 takes 252 registers and the FP64 source reverse would
+// take 262, one wave per SIMD; both are held to two (the reverse spills five registers then).
+// Everything else keeps the compiler's choice.
 template <typename T, int MODE> struct rt_step_waves {
   static constexpr int value = sizeof(T) == 8 && (MODE == 2 || MODE >= 4) ? 2 : 1;
 };
@@ -44,13 +48,17 @@ k_step(rt_step_args a, int64_t nblk) {
   using V4 = typename rt_vec4<T>::type;
   // Runs of two pairs per lane (fewer, wider gathers): at 128^3 x 80 upwind, FP32 with
   // antipodes side by side 1.30 -> 1.18 ms and FP64 with antipodes K/2 on 2.35 -> 2.04 ms
-  // (the other two forms within 3%).  PLM stage 2 addresses its four gathered rows per
-  // element and keeps one pair per slot (the runs made its FP64 form 1.59 -> 2.09 ms).
+  // (the other two forms within 3%).  PLM stage 2 gathers 16-byte parts of states and keeps
+  // one pair per slot.
   using Ang = rt_step_angles<T, LPC, APL, FULL, PAIRED, MODE != 2>;
   constexpr bool FACES = MODE >= 1 && MODE <= 4;  // the modes that read face records
   constexpr bool TRANSPOSE = MODE == 3 || MODE == 4;
+  // PLM stage 2 reads I_in and writes I_out once; past the caches, they leave those to the
+  // gathered states (64^3 x 80 step, FP64 1.343 -> 1.333 ms).  Rows of part lines stay in the
+  // caches: past them a step at 48^3 x 37 took 0.22 ms (FP32) instead of 0.20.
+  constexpr bool NT = MODE == 2 && FULL && LPC * APL * sizeof(T) % 64 == 0;
   constexpr int P = Ang::P;
-  constexpr int U = rt_batch<T, PAIRED>::U;
+  constexpr int U = rt_batch<T, APL, PAIRED>::U;
   constexpr int CPB = RT_BLOCK / LPC;
   extern __shared__ __align__(16) unsigned char rt_smem[];
   V4 *s_an = (V4 *)rt_smem;
@@ -91,7 +99,7 @@ k_step(rt_step_args a, int64_t nblk) {
   const int k_single = Ang::SINGLE ? ang.k[P - 1] : ang.k[0];
   const T *Iin_lane = Iin + ang.k[0], *Iin_single = Iin + k_single;
   T Ic[APL];
-  ang.read_lane(Iin_lane + row, Iin_single + row, Ic);
+  ang.template read_lane<NT>(Iin_lane + row, Iin_single + row, Ic);
 
   double Vnew = 0.0, Vstart = 0.0;
   // the start-of-step volume: the reverse modes take it from the forward step's tape
@@ -157,33 +165,24 @@ k_step(rt_step_args a, int64_t nblk) {
         }
       }
     } else {
-      // reconstructed face states of the half-step intensities (PLM stage 2).  FP32: each cell
-      // and angle's (I_half, limited gradient) is one 16-byte 4-vector ([N][K][4]), so a face
-      // state is one access (64^3 x 80 PLM step 0.94 -> 0.85 ms); FP64 keeps I_half [N][K] and
-      // the gradient [N][3][K] apart (packed, its 32-byte states raised the register pressure
-      // of a kernel already spilling: 1.57 -> 2.07 ms)
-      constexpr bool PACKED = sizeof(T) == 4;
-      const V4 *Pk = (const V4 *)a.grad;
-      const T *Ih = (const T *)a.I_half;
-      const T *G = (const T *)a.grad;
-      T hs[APL], gsx[APL], gsy[APL], gsz[APL];
+      // reconstructed face states of the half-step intensities (PLM stage 2).  Of an antipodal
+      // pair only the direction that enters through a face needs the neighbour's state, so one
+      // state per pair is gathered, chosen by the sign of the face speed, and the second where
+      // both enter.  The kernel is bound by the address and data units of its gathers (80% of the
+      // time, both precisions) and the L2 lines behind them: 64^3 x 80 step with antipodes K/2
+      // apart, FP64 1.64 -> 1.28 ms, side by side (the pair shares its lines) 1.38 -> 1.28;
+      // FP32 0.74 -> 0.69 and 0.71 -> 0.67.  Faces at a third of the light speed, where many
+      // pairs enter whole: FP32 0.326 -> 0.331 ms (48^3 x 80), FP64 0.72 -> 0.61.
+      using S = rt_state<T>;
+      const int KK = FULL ? LPC * APL : K;
+      const typename S::part *states = (const typename S::part *)a.states + ang.k[0];
+      const uint32_t state_row = (uint32_t)(K * sizeof(V4));
+      auto of = [&](uint32_t c) { return (const typename S::part *)((const char *)states + (uint64_t)c * state_row); };
+      auto at = [&](int q) { return FULL ? Ang::slot_offset(q) : ang.k[q] - ang.k[0]; };
+      V4 own[APL];
 #pragma unroll
-      for (int q = 0; q < APL; ++q) {
-        const int k = ang.k[q];
-        if constexpr (PACKED) {
-          const V4 o = Pk[row + k];
-          hs[q] = o.x;
-          gsx[q] = o.y;
-          gsy[q] = o.z;
-          gsz[q] = o.w;
-        } else {
-          hs[q] = Ih[row + k];
-          gsx[q] = G[(cell * 3 + 0) * K + k];
-          gsy[q] = G[(cell * 3 + 1) * K + k];
-          gsz[q] = G[(cell * 3 + 2) * K + k];
-        }
-      }
-      constexpr int UP = sizeof(T) == 4 ? 2 : 1;
+      for (int q = 0; q < APL; ++q) own[q] = S::load(of((uint32_t)cell) + at(q), KK);
+      constexpr int UP = rt_batch<T, APL, PAIRED>::PLM;
       for (int h = h0; h < h1; h += UP) {
         uint32_t j[UP];
         V4 r[UP], r0[UP], r1[UP];
@@ -197,51 +196,45 @@ k_step(rt_step_args a, int64_t nblk) {
           r1[u] = s_rel[2 * i + 1];
           if (!v) r[u] = V4{T(0), T(0), T(0), T(0)};
         }
-        T xh[UP][APL], xg0[UP][APL], xg1[UP][APL], xg2[UP][APL];
-#pragma unroll
-        for (int u = 0; u < UP; ++u) {
-          if constexpr (PACKED) {
-            const V4 *Pj = Pk + (uint64_t)j[u] * K;
-#pragma unroll
-            for (int q = 0; q < APL; ++q) {
-              const V4 o = Pj[ang.k[q]];
-              xh[u][q] = o.x;
-              xg0[u][q] = o.y;
-              xg1[u][q] = o.z;
-              xg2[u][q] = o.w;
-            }
-          } else {
-            const T *Hj = Ih + (uint64_t)j[u] * K;
-            const T *Gj = G + (uint64_t)j[u] * 3 * K;
-#pragma unroll
-            for (int q = 0; q < APL; ++q) {
-              const int k = ang.k[q];
-              xh[u][q] = Hj[k];
-              xg0[u][q] = Gj[k];
-              xg1[u][q] = Gj[K + k];
-              xg2[u][q] = Gj[2 * K + k];
-            }
-          }
-        }
+        T g[UP][P], m2b[UP];
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
           const T ax = sc * r[u].x, ay = sc * r[u].y, az = sc * r[u].z, nb = -(sd * r[u].w);
-          const T m2b = nb + nb;
-          // the charge through the face at the reconstructed state of its upwind side
-          auto face = [&](int q, T g) {
-            const T fs = hs[q] + gsx[q] * r0[u].x + gsy[q] * r0[u].y + gsz[q] * r0[u].z;
-            const T fn = xh[u][q] + xg0[u][q] * r0[u].w + xg1[u][q] * r1[u].x + xg2[u][q] * r1[u].y;
-            acc[q] -= g * (g > T(0) ? fs : fn);
-          };
-          // FP32: the antipode's speed as in the upwind loop (64^3 x 80 PLM step 0.778 ->
-          // 0.760 ms); FP64 keeps three multiply-adds per angle (paired: 1.474 -> 1.489 ms)
-          constexpr bool PAIR_G = PAIRED && sizeof(T) == 4;
-          constexpr int NG = PAIR_G ? P : APL;
+          m2b[u] = nb + nb;
 #pragma unroll
-          for (int q = 0; q < NG; ++q) {
-            const T g = fma(az, ang.dz(q), fma(ay, ang.dy(q), fma(ax, ang.dx(q), nb)));
-            face(q, g);
-            if (PAIR_G) face(q + P, m2b - g);
+          for (int q = 0; q < P; ++q) g[u][q] = fma(az, ang.z[q], fma(ay, ang.y[q], fma(ax, ang.x[q], nb)));
+        }
+        V4 x[UP][P];
+#pragma unroll
+        for (int u = 0; u < UP; ++u) {
+          const typename S::part *n = of(j[u]), *anti = PAIRED ? n + (PAIRED == 2 ? 1 : LPC * P) : n;
+#pragma unroll
+          for (int q = 0; q < P; ++q) x[u][q] = S::load((PAIRED && !(g[u][q] < T(0)) ? anti : n) + at(q), KK);
+        }
+#pragma unroll
+        for (int u = 0; u < UP; ++u) {
+          // the states of the face's two sides
+          auto here = [&](const V4 &o) { return o.x + o.y * r0[u].x + o.z * r0[u].y + o.w * r0[u].z; };
+          auto there = [&](const V4 &o) { return o.x + o.y * r0[u].w + o.z * r1[u].x + o.w * r1[u].y; };
+          bool more = false;  // a face fast enough that both directions of a pair enter through it
+#pragma unroll
+          for (int q = 0; q < P; ++q) {
+            const T n = there(x[u][q]);
+            acc[q] -= g[u][q] * (g[u][q] > T(0) ? here(own[q]) : n);
+            if (PAIRED) {
+              const T g2 = m2b[u] - g[u][q];  // the antipodal angle, as in the upwind loop
+              const bool both = g[u][q] < T(0) && g2 < T(0);
+              const T to = acc[q + P] - g2 * (g2 > T(0) ? here(own[q + P]) : n);
+              acc[q + P] = both ? acc[q + P] : to;
+              more |= both;
+            }
+          }
+          if (PAIRED && more) {
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+              const T g2 = m2b[u] - g[u][q];
+              if (g[u][q] < T(0) && g2 < T(0)) acc[q + P] -= g2 * there(S::load(of(j[u]) + at(q + P), KK));
+            }
           }
         }
       }
@@ -280,7 +273,7 @@ k_step(rt_step_args a, int64_t nblk) {
 
   {
     T *o = (T *)a.I_out + row;
-    ang.write_lane(o + ang.k[0], o + k_single, Ic);
+    ang.template write_lane<NT>(o + ang.k[0], o + k_single, Ic);
   }
   if ((MODE == 1 || MODE == 2) && l == 0 && a.vol_out) a.vol_out[cell] = Vnew;
   if (MODE == 1 && l == 0 && a.src_tape_out) a.src_tape_out[RT_SRC_TAPE * cell + RT_TAPE_V] = Vstart;

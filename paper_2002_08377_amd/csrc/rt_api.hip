@@ -208,14 +208,13 @@ int run_step(rt_mesh *m, const rt_params *p, const rt_angles *a, const void *I_i
   s1.write_gas = 0;
   hipError_t e = rt_launch_step(s1, p->dtype, st);
   if (e != hipSuccess) return hip_fail(e, "stage-1 kernel launch");
-  // FP32: (I_half, gradient) packed per cell and angle for stage 2; FP64: the gradient alone
-  e = rt_launch_gradient(m, a->K, m->I_half, m->grad, p->dtype, p->dtype == RT_F32, st);
+  // (I_half, gradient) packed per cell and angle for stage 2
+  e = rt_launch_gradient(m, a->K, m->I_half, m->states, p->dtype, true, st);
   if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
   // stage 2: reconstructed fluxes of the half-step state on the start-of-step charges, source on gas^n
   rt_step_args s2 = s;
   s2.I_in = I_in;
-  s2.I_half = m->I_half;
-  s2.grad = m->grad;
+  s2.states = m->states;
   s2.I_out = I_out;
   s2.vol_in = vol;
   s2.vol_out = vol;
@@ -396,7 +395,7 @@ int rt_mesh_upload(rt_mesh **out, int64_t N, int64_t F, int32_t k_max, int32_t f
     RT_ALLOC(m->gb64, sizeof(double4) * N);
     RT_ALLOC(m->gb32, sizeof(float4) * N);
     RT_ALLOC(m->I_half, sizeof(double) * N * k_max);
-    RT_ALLOC(m->grad, sizeof(double) * 4 * N * k_max);
+    RT_ALLOC(m->states, sizeof(double) * 4 * N * k_max);
   }
   if (flags & RT_MESH_ADJOINT) RT_ALLOC(m->lam_star, sizeof(double) * N * k_max);
   RT_ALLOC(m->red, sizeof(double) * RT_NDIAG * nred);

@@ -33,8 +33,7 @@ struct rt_mesh {
   float4 *gb32;
   // scratch
   void *I_half;       // [N][k_max] doubles (RT_MESH_PLM), used in either precision
-  void *grad;         // RT_MESH_PLM, 4 N k_max doubles: FP32 (I_half, limited gradient) per cell
-                     // and angle [N][K][4]; FP64 the limited gradient [N][3][K]
+  void *states;       // RT_MESH_PLM, 4 N k_max doubles: (I_half, limited gradient) per cell and angle
   void *lam_star;     // [N][k_max] doubles (RT_MESH_ADJOINT)
   double *red;        // reduction partials, RT_NDIAG * n_red_blocks doubles
   double *red_mid;    // first fold of the partials, RT_NDIAG * RT_BLOCK doubles
@@ -64,8 +63,7 @@ struct rt_step_args {
   const double *dirs;
   const double *W;
   const void *I_in;    // intensities read by transport (start-of-step charges)
-  const void *I_half;  // PLM stage 2: half-step intensities (face states)
-  const void *grad;    // PLM stage 2: FP32 (I_half, limited gradient) [N][K][4]; FP64 gradient [N][3][K]
+  const void *states;  // PLM stage 2: half-step intensities and limited gradients, as rt_state lays them out
   void *I_out;
   void *I_star_out;    // upwind with source: when set, the transported intensities (the
                        // source's input) are stored here as well

@@ -81,26 +81,24 @@ template <typename T, int LPC, int APL, bool FULL, int PAIRED, bool TWOS = false
   __device__ __forceinline__ const T *lane_row(const T *lane_base, uint32_t r, uint32_t row_bytes) const {
     return (const T *)((const char *)lane_base + (uint64_t)r * row_bytes);
   }
+  template <bool NT = false>
   __device__ __forceinline__ void read_lane(const T *pl, const T *ps, T (&v)[APL]) const {
     if constexpr (FULL) {
 #pragma unroll
-      for (int q = 0; q < APL; ++q) v[q] = is_single(q) ? ps[slot_offset(q)] : pl[slot_offset(q)];
+      for (int q = 0; q < APL; ++q) v[q] = rt_get<NT>(is_single(q) ? ps + slot_offset(q) : pl + slot_offset(q));
     } else {
 #pragma unroll
-      for (int q = 0; q < APL; ++q) v[q] = pl[k[q] - k[0]];
+      for (int q = 0; q < APL; ++q) v[q] = rt_get<NT>(pl + (k[q] - k[0]));
     }
   }
-  __device__ __forceinline__ void write_lane(T *pl, T *ps, const T (&v)[APL]) const {
+  template <bool NT = false> __device__ __forceinline__ void write_lane(T *pl, T *ps, const T (&v)[APL]) const {
     if constexpr (FULL) {
 #pragma unroll
-      for (int q = 0; q < APL; ++q) {
-        if (is_single(q)) ps[slot_offset(q)] = v[q];
-        else pl[slot_offset(q)] = v[q];
-      }
+      for (int q = 0; q < APL; ++q) rt_put<NT>(is_single(q) ? ps + slot_offset(q) : pl + slot_offset(q), v[q]);
     } else {
 #pragma unroll
       for (int q = 0; q < APL; ++q)
-        if (ok[q]) pl[k[q] - k[0]] = v[q];
+        if (ok[q]) rt_put<NT>(pl + (k[q] - k[0]), v[q]);
     }
   }
   __device__ __forceinline__ void write_row(T *p, const T (&v)[APL]) const {
