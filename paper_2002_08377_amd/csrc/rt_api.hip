@@ -227,6 +227,38 @@ int run_step(rt_mesh *m, const rt_params *p, const rt_angles *a, const void *I_i
   return RT_OK;
 }
 
+rt_mg_args mg_args(const rt_mesh *m, const rt_params *p, const rt_angles *a, int32_t G, const double *group_weight,
+                   void *I, const double *rho, double *mom, double *etot, const double *kP, const double *kJ,
+                   const double *ks, double *T_new) {
+  rt_mg_args g;
+  memset(&g, 0, sizeof g);
+  g.N = m->N;
+  g.K = a->K;
+  g.G = G;
+  g.paired = rt_pair_kind(a->layout);
+  g.dirs = a->dir;
+  g.W = a->weight;
+  g.Wg = group_weight;
+  g.I = I;
+  g.rho = rho;
+  g.mom = mom;
+  g.etot = etot;
+  g.kP = kP;
+  g.kJ = kJ;
+  g.ks = ks;
+  g.T_out = T_new;
+  g.c_red = p->c_red;
+  g.c_light = p->c_light;
+  g.a_rad = p->a_rad;
+  g.cv = p->cv;
+  g.dt = p->dt;
+  g.inv_c = 1.0 / p->c_light;
+  g.e_gain = 4.0 * M_PI * p->c_light / p->c_red;
+  g.m_gain = 4.0 * M_PI / p->c_red;
+  g.a_4pi = p->a_rad / (4.0 * M_PI);
+  return g;
+}
+
 }  // namespace
 
 extern "C" {
@@ -712,32 +744,7 @@ int rt_source_implicit_mg(rt_mesh *m, const rt_params *p, const rt_angles *a, in
   if (rc) return rc;
   if (G < 1 || G > RT_G_MAX) return fail(RT_EINVAL, "G=%d outside [1, %d]", G, RT_G_MAX);
   if ((rc = check_ptrs({group_weight, I, rho, mom, etot, kP, kJ, ks}))) return rc;
-  rt_mg_args g;
-  memset(&g, 0, sizeof g);
-  g.N = m->N;
-  g.K = a->K;
-  g.G = G;
-  g.paired = rt_pair_kind(a->layout);
-  g.dirs = a->dir;
-  g.W = a->weight;
-  g.Wg = group_weight;
-  g.I = I;
-  g.rho = rho;
-  g.mom = mom;
-  g.etot = etot;
-  g.kP = kP;
-  g.kJ = kJ;
-  g.ks = ks;
-  g.T_out = T_new;
-  g.c_red = p->c_red;
-  g.c_light = p->c_light;
-  g.a_rad = p->a_rad;
-  g.cv = p->cv;
-  g.dt = p->dt;
-  g.inv_c = 1.0 / p->c_light;
-  g.e_gain = 4.0 * M_PI * p->c_light / p->c_red;
-  g.m_gain = 4.0 * M_PI / p->c_red;
-  g.a_4pi = p->a_rad / (4.0 * M_PI);
+  const rt_mg_args g = mg_args(m, p, a, G, group_weight, I, rho, mom, etot, kP, kJ, ks, T_new);
   hipError_t e = rt_launch_source_mg(g, p->dtype, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "multigroup source kernel launch");
   return RT_OK;
@@ -754,6 +761,17 @@ int rt_step_mg(rt_mesh *m, const rt_params *p, const rt_angles *a, int32_t G, co
   const size_t slab = elem(p->dtype) * m->N * a->K;
   if (overlap(I_in, I_out, slab * G)) return fail(RT_EINVAL, "I_in and I_out overlap");
   hipStream_t st = (hipStream_t)stream;
+  {
+    rt_step_args s = base_args(m, p, a);
+    s.I_in = I_in;
+    s.I_out = I_out;
+    s.vol_in = vol;
+    s.vol_out = vol;
+    const rt_mg_args g = mg_args(m, p, a, G, group_weight, I_out, rho, mom, etot, kP, kJ, ks, T_new);
+    const hipError_t e = rt_launch_step_mg(s, g, p->dtype, st);
+    if (e == hipSuccess) return RT_OK;
+    if (e != hipErrorInvalidConfiguration) return hip_fail(e, "multigroup step kernel launch");
+  }
   // every group's slab is transported by the upwind kernel; the volume advances once
   for (int32_t j = 0; j < G; ++j) {
     rt_step_args s = base_args(m, p, a);

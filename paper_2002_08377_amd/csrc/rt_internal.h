@@ -193,6 +193,8 @@ struct rt_mg_args {
   double inv_c, e_gain, m_gain, a_4pi;
 };
 hipError_t rt_launch_source_mg(const rt_mg_args &a, int dtype, hipStream_t s);
+// the whole step in one kernel; hipErrorInvalidConfiguration where its rows do not fit in LDS
+hipError_t rt_launch_step_mg(const rt_step_args &a, const rt_mg_args &m, int dtype, hipStream_t s);
 
 // Source with power-law temperature-dependent opacities.
 struct rt_kT_args {
