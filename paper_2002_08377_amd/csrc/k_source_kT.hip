@@ -52,24 +52,14 @@ __device__ __forceinline__ double rt_half_power(double x, int half2) {
 template <int APL, int PAIRED, bool HALF> struct rt_kT_waves {
   static constexpr int value = HALF && (!PAIRED || APL <= 10) ? 3 : PAIRED && APL > 10 ? 1 : 2;
 };
-template <typename T, int LPC, int APL, bool FULL, int PAIRED, bool HALF>
-__global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_kT_waves<APL, PAIRED, HALF>::value))) void
-k_source_kT(rt_kT_args a, int64_t nblk) {
-  using Ang = rt_step_angles<double, LPC, APL, FULL, PAIRED>;
-  constexpr int CPB = RT_BLOCK / LPC;
-  __shared__ double s_dir[3 * RT_K_MAX], s_w[RT_K_MAX];
-  const int64_t lb = rt_logical_block(nblk);
-  if (lb < 0) return;  // whole workgroup
+// The update of one cell.  row: its incoming intensities, .first(ang, q) before the iteration and
+// .again(ang, q) after it, and .store(ang, out) for the updated ones.
+template <typename T, int LPC, int APL, bool HALF, typename Ang, typename Row>
+__device__ __forceinline__ void rt_kT_cell(const rt_kT_args &a, const double *s_dir, const double *s_w, int64_t cell,
+                                           int l, const Row &row) {
   const int K = a.K;
-  for (int i = threadIdx.x; i < 3 * K; i += RT_BLOCK) s_dir[i] = a.dirs[i];
-  for (int i = threadIdx.x; i < K; i += RT_BLOCK) s_w[i] = a.W[i];
-  __syncthreads();
-  const int64_t cell = lb * CPB + threadIdx.x / LPC;
-  if (cell >= a.N) return;
-  const int l = threadIdx.x % LPC;
   Ang ang;
   ang.load(s_dir, s_w, K, l);
-  T *Ir = (T *)a.I + cell * (int64_t)K;
 
   const double rho = a.rho[cell];
   const double m0 = a.mom[3 * cell], m1 = a.mom[3 * cell + 1], m2 = a.mom[3 * cell + 2];
@@ -83,7 +73,7 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
   double norm = 0.0;
 #pragma unroll
   for (int q = 0; q < APL; ++q) {
-    const double I0 = (double)Ir[ang.k[q]];
+    const double I0 = (double)row.first(ang, q);
     const double vn = vx * ang.dx(q) + vy * ang.dy(q) + vz * ang.dz(q);
     Gm[q] = gam * (1.0 - vn * ic);
     const double iG = rt_rcp(Gm[q]);
@@ -224,20 +214,21 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
   const double Jc = (e.SI + y * e.kP * e.SG * planck) * rt_rcp(e.D);
   const double yS = y * (e.kP * planck + ks * Jc), yc = y * (e.kJ + ks);
   double dE = 0, dFx = 0, dFy = 0, dFz = 0;
+  T out[APL];
 #pragma unroll
   for (int q = 0; q < APL; ++q) {
     // I' = (Gamma^4 I + y Gamma S) r / Gamma^4 = r (I + y S / Gamma^3), the incoming value
     // read again rather than held through the iteration
-    const double I0 = (double)Ir[ang.k[q]];
+    const double I0 = (double)row.again(ang, q);
     const double iG = rt_rcp(Gm[q]);
-    const T out = (T)((I0 + yS * (iG * iG * iG)) * rt_rcp(1.0 + yc * Gm[q]));
-    const double wd = ang.wt(q) * (I0 - (double)out);
-    if (ang.ok[q]) Ir[ang.k[q]] = out;
+    out[q] = (T)((I0 + yS * (iG * iG * iG)) * rt_rcp(1.0 + yc * Gm[q]));
+    const double wd = ang.wt(q) * (I0 - (double)out[q]);
     dE += wd;
     dFx += wd * ang.dx(q);
     dFy += wd * ang.dy(q);
     dFz += wd * ang.dz(q);
   }
+  row.store(ang, out);
   dE = rt_group_sum<LPC>(dE);
   dFx = rt_group_sum<LPC>(dFx);
   dFy = rt_group_sum<LPC>(dFy);
@@ -251,59 +242,194 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
   }
 }
 
-template <typename T, int LPC, int APL, bool FULL, int PAIRED>
-hipError_t launch(const rt_kT_args &args, hipStream_t s) {
-  rt_kT_args a = args;
-  a.bP2 = (int)(2.0 * a.bP);
-  a.bJ2 = (int)(2.0 * a.bJ);
-  const bool half = a.bP2 == 2.0 * a.bP && a.bJ2 == 2.0 * a.bJ;
-  const int64_t cpb = RT_BLOCK / LPC;
-  const int64_t nblk = (a.N + cpb - 1) / cpb;
-  const dim3 grid((unsigned)rt_grid_for(nblk)), block(RT_BLOCK);
-  if (half) hipLaunchKernelGGL((k_source_kT<T, LPC, APL, FULL, PAIRED, true>), grid, block, 0, s, a, nblk);
-  else hipLaunchKernelGGL((k_source_kT<T, LPC, APL, FULL, PAIRED, false>), grid, block, 0, s, a, nblk);
-  return hipGetLastError();
+__device__ __forceinline__ void rt_kT_stage_angles(const rt_kT_args &a, double *s_dir, double *s_w) {
+  for (int i = threadIdx.x; i < 3 * a.K; i += RT_BLOCK) s_dir[i] = a.dirs[i];
+  for (int i = threadIdx.x; i < a.K; i += RT_BLOCK) s_w[i] = a.W[i];
 }
 
-template <typename T, int PAIRED> hipError_t dispatch_paired(const rt_kT_args &a, hipStream_t s) {
-  switch (rt_paired_lanes(a.K)) {  // 0 (no paired layout for K) matches no case
-    case 0x0802: return launch<T, 8, 2, true, PAIRED>(a, s);
-    case 0x0804: return launch<T, 8, 4, true, PAIRED>(a, s);
-    case 0x0806: return launch<T, 8, 6, true, PAIRED>(a, s);
-    case 0x0808: return launch<T, 8, 8, true, PAIRED>(a, s);
-    case 0x080a: return launch<T, 8, 10, true, PAIRED>(a, s);
-    case 0x080c: return launch<T, 8, 12, true, PAIRED>(a, s);
-    case 0x0402: return launch<T, 4, 2, true, PAIRED>(a, s);
-    case 0x0406: return launch<T, 4, 6, true, PAIRED>(a, s);
-    case 0x040a: return launch<T, 4, 10, true, PAIRED>(a, s);
+template <typename T, int LPC, int APL, bool FULL, int PAIRED, bool HALF>
+__global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_kT_waves<APL, PAIRED, HALF>::value))) void
+k_source_kT(rt_kT_args a, int64_t nblk) {
+  using Ang = rt_step_angles<double, LPC, APL, FULL, PAIRED>;
+  constexpr int CPB = RT_BLOCK / LPC;
+  __shared__ double s_dir[3 * RT_K_MAX], s_w[RT_K_MAX];
+  const int64_t lb = rt_logical_block(nblk);
+  if (lb < 0) return;  // whole workgroup
+  rt_kT_stage_angles(a, s_dir, s_w);
+  __syncthreads();
+  const int64_t cell = lb * CPB + threadIdx.x / LPC;
+  if (cell >= a.N) return;
+  struct Row {
+    T *I;
+    __device__ __forceinline__ T first(const Ang &ang, int q) const { return I[ang.k[q]]; }
+    __device__ __forceinline__ T again(const Ang &ang, int q) const { return I[ang.k[q]]; }
+    __device__ __forceinline__ void store(const Ang &ang, const T (&v)[APL]) const {
+#pragma unroll
+      for (int q = 0; q < APL; ++q)
+        if (ang.ok[q]) I[ang.k[q]] = v[q];
+    }
+  };
+  rt_kT_cell<T, LPC, APL, HALF, Ang>(a, s_dir, s_w, cell, threadIdx.x % LPC, Row{(T *)a.I + cell * (int64_t)a.K});
+}
+
+// The step: upwind transport into registers, then the source.  As two launches the transported
+// intensities were written, read twice and written again, and the transport (bound by its
+// gathers) and the source (bound by FP64 issue) each left the other's unit idle.  The
+// transported values wait in LDS, in words of the lane's own, through the iteration.
+// 64^3 x 80, exponent -3.5, FP32: 350 -> 319 us; 12^3 x 24 FP64 24.4 -> 21.8.  FP64 rows of
+// 10 angles per lane gain only at two waves per SIMD (48^3 x 80: 172 -> 165 us; 173 at three).
+template <typename T, int APL, int PAIRED, bool HALF> struct rt_kT_step_waves {
+  static constexpr int value = sizeof(T) == 8 && PAIRED && APL == 10 ? 2 : rt_kT_waves<APL, PAIRED, HALF>::value;
+};
+template <typename T, int LPC, int APL, bool FULL, int PAIRED, bool HALF>
+__global__ __launch_bounds__(RT_BLOCK)
+__attribute__((amdgpu_waves_per_eu(rt_kT_step_waves<T, APL, PAIRED, HALF>::value))) void
+k_step_kT(rt_step_args t, rt_kT_args a, int64_t nblk) {
+  using V4 = typename rt_vec4<T>::type;
+  using AngT = rt_step_angles<T, LPC, APL, FULL, PAIRED, true>;
+  using Ang = rt_step_angles<double, LPC, APL, FULL, PAIRED, true>;  // the same slots
+  constexpr int CPB = RT_BLOCK / LPC;
+  __shared__ double s_dir[3 * RT_K_MAX], s_w[RT_K_MAX];
+  __shared__ T s_rows[APL * RT_BLOCK];
+  extern __shared__ __align__(16) unsigned char rt_smem[];
+  V4 *s_an = (V4 *)rt_smem;
+  int32_t *s_nbr = (int32_t *)(s_an + t.hf_cap);
+  const int64_t lb = rt_logical_block(nblk);
+  if (lb < 0) return;  // whole workgroup
+  const int64_t c0 = lb * CPB, c1 = c0 + CPB < t.N ? c0 + CPB : t.N;
+  const int g = threadIdx.x / LPC, l = threadIdx.x % LPC;
+  const bool live = c0 + g < t.N;
+  const int64_t cell = live ? c0 + t.wg_order[c0 + g] : c0;
+  const int H0 = t.row_ptr[c0];
+  {
+    const V4 *an = (const V4 *)t.hf_an;
+    const int nH = t.row_ptr[c1] - H0;  // <= hf_cap by construction
+    for (int i = threadIdx.x; i < nH; i += RT_BLOCK) {
+      s_nbr[i] = t.hf_nbr[H0 + i];
+      s_an[i] = an[H0 + i];
+    }
+  }
+  rt_kT_stage_angles(a, s_dir, s_w);
+  __syncthreads();
+  if (!live) return;
+  T I[1][APL];
+  {
+    AngT ang;
+    ang.load(t.dirs, t.W, t.K, l);
+    const int k_single = AngT::SINGLE ? ang.k[AngT::P - 1] : ang.k[0];
+    const double dD = t.D[cell];
+    const double Vnew = rt_vol_next(t.vol_in[cell], t.dt, dD);
+    const double iV = rt_rcp(Vnew);
+    const int h0 = t.row_ptr[cell] - H0, nh = t.row_ptr[cell + 1] - H0 - h0;
+    rt_upwind_sweep<T, LPC, APL, 1>(t, ang, 0, cell, (const T *)t.I_in, k_single, s_nbr + h0, s_an + h0, nh,
+                                    (T)(1.0 - t.dt * dD * iV), (T)iV, I);
+    if (l == 0) t.vol_out[cell] = Vnew;
+  }
+  T *own = s_rows + threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < APL; ++q) own[q * RT_BLOCK] = I[0][q];
+  struct Row {
+    const T *own;
+    T *out;
+    __device__ __forceinline__ T first(const Ang &, int q) const { return own[q * RT_BLOCK]; }
+    __device__ __forceinline__ T again(const Ang &, int q) const { return own[q * RT_BLOCK]; }
+    __device__ __forceinline__ void store(const Ang &ang, const T (&v)[APL]) const {
+#pragma unroll
+      for (int q = 0; q < APL; ++q)
+        if (ang.ok[q]) out[ang.k[q]] = v[q];
+    }
+  };
+  rt_kT_cell<T, LPC, APL, HALF, Ang>(a, s_dir, s_w, cell, l, Row{own, (T *)t.I_out + cell * (int64_t)t.K});
+}
+
+rt_kT_args with_powers(rt_kT_args a, bool &half) {
+  a.bP2 = (int)(2.0 * a.bP);
+  a.bJ2 = (int)(2.0 * a.bJ);
+  half = a.bP2 == 2.0 * a.bP && a.bJ2 == 2.0 * a.bJ;
+  return a;
+}
+
+struct rt_source_only {
+  rt_kT_args a;
+  int K() const { return a.K; }
+  int paired() const { return a.paired; }
+  template <typename T, int LPC, int APL, bool FULL, int PAIRED> hipError_t run(hipStream_t s) const {
+    bool half;
+    const rt_kT_args b = with_powers(a, half);
+    const int64_t cpb = RT_BLOCK / LPC;
+    const int64_t nblk = (b.N + cpb - 1) / cpb;
+    const dim3 grid((unsigned)rt_grid_for(nblk)), block(RT_BLOCK);
+    if (half) hipLaunchKernelGGL((k_source_kT<T, LPC, APL, FULL, PAIRED, true>), grid, block, 0, s, b, nblk);
+    else hipLaunchKernelGGL((k_source_kT<T, LPC, APL, FULL, PAIRED, false>), grid, block, 0, s, b, nblk);
+    return hipGetLastError();
+  }
+};
+
+// hipErrorInvalidConfiguration: the step takes its separate launches.
+struct rt_whole_step {
+  rt_step_args t;
+  rt_kT_args a;
+  int K() const { return a.K; }
+  int paired() const { return a.paired; }
+  template <typename T, int LPC, int APL, bool FULL, int PAIRED> hipError_t run(hipStream_t s) const {
+    bool half;
+    const rt_kT_args b = with_powers(a, half);
+    rt_step_args u = t;
+    u.hf_cap = LPC == 16 ? t.hf_cap16 : LPC == 8 ? t.hf_cap32 : t.hf_cap64;
+    u.wg_order = LPC == 16 ? t.wg_order16 : LPC == 8 ? t.wg_order32 : t.wg_order64;
+    const int64_t cpb = RT_BLOCK / LPC;
+    const int64_t nblk = (b.N + cpb - 1) / cpb;
+    const dim3 grid((unsigned)rt_grid_for(nblk)), block(RT_BLOCK);
+    const size_t smem = (sizeof(typename rt_vec4<T>::type) + sizeof(int32_t)) * (size_t)u.hf_cap;
+    const size_t fixed = sizeof(double) * 4 * RT_K_MAX + sizeof(T) * APL * RT_BLOCK;
+    // two workgroups per CU at least, as the separate launches have at the same face counts
+    if (smem + fixed > (size_t)t.lds_max / 2) return hipErrorInvalidConfiguration;
+    if (half) hipLaunchKernelGGL((k_step_kT<T, LPC, APL, FULL, PAIRED, true>), grid, block, smem, s, u, b, nblk);
+    else hipLaunchKernelGGL((k_step_kT<T, LPC, APL, FULL, PAIRED, false>), grid, block, smem, s, u, b, nblk);
+    return hipGetLastError();
+  }
+};
+
+// OP is the launch to make in the layout chosen: the source alone, or the step.
+template <typename T, int PAIRED, typename OP> hipError_t dispatch_paired(const OP &op, hipStream_t s) {
+  switch (rt_paired_lanes(op.K())) {  // 0 (no paired layout for K) matches no case
+    case 0x0802: return op.template run<T, 8, 2, true, PAIRED>(s);
+    case 0x0804: return op.template run<T, 8, 4, true, PAIRED>(s);
+    case 0x0806: return op.template run<T, 8, 6, true, PAIRED>(s);
+    case 0x0808: return op.template run<T, 8, 8, true, PAIRED>(s);
+    case 0x080a: return op.template run<T, 8, 10, true, PAIRED>(s);
+    case 0x080c: return op.template run<T, 8, 12, true, PAIRED>(s);
+    case 0x0402: return op.template run<T, 4, 2, true, PAIRED>(s);
+    case 0x0406: return op.template run<T, 4, 6, true, PAIRED>(s);
+    case 0x040a: return op.template run<T, 4, 10, true, PAIRED>(s);
   }
   return hipErrorInvalidConfiguration;
 }
 
 // Antipodal sets with a paired layout put 4 or 8 lanes on a cell (more cells per wave, so the
 // per-cell scalar work of each evaluation is shared by fewer lanes); others the general one.
-template <typename T> hipError_t dispatch(const rt_kT_args &a, hipStream_t s) {
-  if (a.paired) {
-    const hipError_t e = a.paired == 2 ? dispatch_paired<T, 2>(a, s) : dispatch_paired<T, 1>(a, s);
+template <typename T, typename OP> hipError_t dispatch(const OP &op, hipStream_t s) {
+  if (op.paired()) {
+    const hipError_t e = op.paired() == 2 ? dispatch_paired<T, 2>(op, s) : dispatch_paired<T, 1>(op, s);
     if (e != hipErrorInvalidConfiguration) return e;
   }
-  switch (rt_step_lanes(a.K, 0)) {
-    case 0x1001: return launch<T, 16, 1, false, 0>(a, s);
-    case 0x1002: return launch<T, 16, 2, false, 0>(a, s);
-    case 0x1003: return launch<T, 16, 3, false, 0>(a, s);
-    case 0x1004: return launch<T, 16, 4, false, 0>(a, s);
-    case 0x1005: return launch<T, 16, 5, false, 0>(a, s);
-    case 0x1006: return launch<T, 16, 6, false, 0>(a, s);
-    case 0x1007: return launch<T, 16, 7, false, 0>(a, s);
-    case 0x1008: return launch<T, 16, 8, false, 0>(a, s);
-    case 0x0801: return launch<T, 8, 1, false, 0>(a, s);
-    case 0x0802: return launch<T, 8, 2, false, 0>(a, s);
-    case 0x0803: return launch<T, 8, 3, false, 0>(a, s);
-    case 0x0804: return launch<T, 8, 4, false, 0>(a, s);
-    case 0x0805: return launch<T, 8, 5, false, 0>(a, s);
-    case 0x0806: return launch<T, 8, 6, false, 0>(a, s);
-    case 0x0807: return launch<T, 8, 7, false, 0>(a, s);
-    case 0x0808: return launch<T, 8, 8, false, 0>(a, s);
+  switch (rt_step_lanes(op.K(), 0)) {
+    case 0x1001: return op.template run<T, 16, 1, false, 0>(s);
+    case 0x1002: return op.template run<T, 16, 2, false, 0>(s);
+    case 0x1003: return op.template run<T, 16, 3, false, 0>(s);
+    case 0x1004: return op.template run<T, 16, 4, false, 0>(s);
+    case 0x1005: return op.template run<T, 16, 5, false, 0>(s);
+    case 0x1006: return op.template run<T, 16, 6, false, 0>(s);
+    case 0x1007: return op.template run<T, 16, 7, false, 0>(s);
+    case 0x1008: return op.template run<T, 16, 8, false, 0>(s);
+    case 0x0801: return op.template run<T, 8, 1, false, 0>(s);
+    case 0x0802: return op.template run<T, 8, 2, false, 0>(s);
+    case 0x0803: return op.template run<T, 8, 3, false, 0>(s);
+    case 0x0804: return op.template run<T, 8, 4, false, 0>(s);
+    case 0x0805: return op.template run<T, 8, 5, false, 0>(s);
+    case 0x0806: return op.template run<T, 8, 6, false, 0>(s);
+    case 0x0807: return op.template run<T, 8, 7, false, 0>(s);
+    case 0x0808: return op.template run<T, 8, 8, false, 0>(s);
   }
   return hipErrorInvalidValue;
 }
@@ -311,5 +437,11 @@ template <typename T> hipError_t dispatch(const rt_kT_args &a, hipStream_t s) {
 }  // namespace
 
 hipError_t rt_launch_source_kT(const rt_kT_args &a, int dtype, hipStream_t s) {
-  return dtype == RT_F32 ? dispatch<float>(a, s) : dispatch<double>(a, s);
+  const rt_source_only op{a};
+  return dtype == RT_F32 ? dispatch<float>(op, s) : dispatch<double>(op, s);
+}
+
+hipError_t rt_launch_step_kT(const rt_step_args &t, const rt_kT_args &a, int dtype, hipStream_t s) {
+  const rt_whole_step op{t, a};
+  return dtype == RT_F32 ? dispatch<float>(op, s) : dispatch<double>(op, s);
 }

@@ -203,68 +203,6 @@ __global__ __launch_bounds__(RT_BLOCK) void k_source_mg(rt_mg_args a, int64_t nb
 // words of the lane's own (no other lane reads them).  0.818 -> 0.602 ms (FP32); FP64 at
 // 48^3 x 80 0.53 -> 0.38, 12^3 x 24 43 -> 27 us.  Bound now by the gathers and the vector
 // issue of the faces, at three waves per SIMD (FP32; held to four it spills and takes 0.69 ms).
-template <typename T, int LPC, int APL, int JG, typename Ang>
-__device__ __forceinline__ void rt_mg_transport(const rt_step_args &a, const Ang &ang, int64_t slab, int64_t cell,
-                                                const T *Iin, int k_single, const int32_t *nbr,
-                                                const typename rt_vec4<T>::type *an, int nh, T cr, T ci,
-                                                T (&Is)[JG][APL]) {
-  using V4 = typename rt_vec4<T>::type;
-  constexpr int P = Ang::P;
-  constexpr bool PAIRED = Ang::PAIRED_LAYOUT;
-  constexpr int U = 2 / JG;  // faces per batch: two rows in flight, as in the single-group step
-  const uint32_t row_bytes = (uint32_t)(a.K * sizeof(T));
-  const T sc = (T)(a.dt * a.c_red), sd = (T)a.dt;
-  T acc[JG][APL];
-  const T *lane[JG], *single[JG];
-#pragma unroll
-  for (int j = 0; j < JG; ++j) {
-    lane[j] = Iin + j * slab + ang.k[0];
-    single[j] = Iin + j * slab + k_single;
-    ang.read_lane(ang.lane_row(lane[j], (uint32_t)cell, row_bytes), ang.lane_row(single[j], (uint32_t)cell, row_bytes),
-                  Is[j]);
-#pragma unroll
-    for (int q = 0; q < APL; ++q) acc[j][q] = T(0);
-  }
-  for (int h = 0; h < nh; h += U) {
-    uint32_t n[U];
-    V4 r[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool v = h + u < nh;
-      const int i = v ? h + u : 0;
-      n[u] = (uint32_t)nbr[i];
-      r[u] = an[i];
-      if (!v) r[u] = V4{T(0), T(0), T(0), T(0)};
-    }
-    T xn[U][JG][APL];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int j = 0; j < JG; ++j)
-        ang.read_lane(ang.lane_row(lane[j], n[u], row_bytes), ang.lane_row(single[j], n[u], row_bytes), xn[u][j]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      // the face speeds of the upwind step, and for every group its charge
-      const T ax = sc * r[u].x, ay = sc * r[u].y, az = sc * r[u].z, nb = -(sd * r[u].w);
-      const T m2b = nb + nb;
-#pragma unroll
-      for (int q = 0; q < P; ++q) {
-        const T g = fma(az, ang.z[q], fma(ay, ang.y[q], fma(ax, ang.x[q], nb)));
-        const T g2 = m2b - g;
-#pragma unroll
-        for (int j = 0; j < JG; ++j) {
-          acc[j][q] -= g * (g > T(0) ? Is[j][q] : xn[u][j][q]);
-          if (PAIRED) acc[j][q + P] -= g2 * (g2 > T(0) ? Is[j][q + P] : xn[u][j][q + P]);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < JG; ++j)
-#pragma unroll
-    for (int q = 0; q < APL; ++q) Is[j][q] = Is[j][q] * cr + acc[j][q] * ci;
-}
-
 // groups whose rows wait in LDS: all but the last sweep's two (a lone group's waits there)
 __host__ __device__ constexpr int rt_mg_rows(int G) { return G > 2 ? G - 2 : G == 1 ? 1 : 0; }
 
@@ -383,7 +321,7 @@ __global__ __launch_bounds__(RT_BLOCK) void k_step_mg(rt_step_args a, rt_mg_args
   if (G % JG) {  // (JG = 2) an odd group first, so that the last sweep is a full one
     T I[1][APL];
     const kappas k = kappa(0);
-    rt_mg_transport<T, LPC, APL, 1>(a, ang, slab, cell, Iin, k_single, nbr, an, nh, cr, ci, I);
+    rt_upwind_sweep<T, LPC, APL, 1>(a, ang, slab, cell, Iin, k_single, nbr, an, nh, cr, ci, I);
     sums(0, k, I[0]);
 #pragma unroll
     for (int q = 0; q < APL; ++q) rows[q * RT_BLOCK] = I[0][q];
@@ -394,7 +332,7 @@ __global__ __launch_bounds__(RT_BLOCK) void k_step_mg(rt_step_args a, rt_mg_args
     kappas k[JG];  // behind the sweep their latency would show: 0.63 against 0.61 ms (64^3 x 80, 4 groups)
 #pragma unroll
     for (int i = 0; i < JG; ++i) k[i] = kappa(j + i);
-    rt_mg_transport<T, LPC, APL, JG>(a, ang, slab, cell, Iin + j * slab, k_single, nbr, an, nh, cr, ci, last);
+    rt_upwind_sweep<T, LPC, APL, JG>(a, ang, slab, cell, Iin + j * slab, k_single, nbr, an, nh, cr, ci, last);
 #pragma unroll
     for (int i = 0; i < JG; ++i) sums(j + i, k[i], last[i]);
     if (j + JG < G) {

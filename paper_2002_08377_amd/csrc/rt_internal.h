@@ -215,6 +215,8 @@ struct rt_kT_args {
   int paired;  // rt_pair_kind of the angle layout
 };
 hipError_t rt_launch_source_kT(const rt_kT_args &a, int dtype, hipStream_t s);
+// the step in one kernel; hipErrorInvalidConfiguration where its face records do not fit in LDS
+hipError_t rt_launch_step_kT(const rt_step_args &t, const rt_kT_args &a, int dtype, hipStream_t s);
 
 // Marked cells (boundary / emitter) resident on the device.
 struct rt_marked {

@@ -108,6 +108,71 @@ template <typename T, int LPC, int APL, bool FULL, int PAIRED, bool TWOS = false
   }
 };
 
+// Upwind transport of one cell's row in JG slabs of intensities at once (slab j starts at
+// Iin + j slab), through its nh faces with records `an` and neighbours `nbr` in LDS: the
+// transported values of the lane's angles.  cr = V/V', ci = 1/V'.
+template <typename T, int LPC, int APL, int JG, typename Ang>
+__device__ __forceinline__ void rt_upwind_sweep(const rt_step_args &a, const Ang &ang, int64_t slab, int64_t cell,
+                                                const T *Iin, int k_single, const int32_t *nbr,
+                                                const typename rt_vec4<T>::type *an, int nh, T cr, T ci,
+                                                T (&Is)[JG][APL]) {
+  using V4 = typename rt_vec4<T>::type;
+  constexpr int P = Ang::P;
+  constexpr bool PAIRED = Ang::PAIRED_LAYOUT;
+  constexpr int U = 2 / JG;  // faces per batch: two rows in flight, as in the single-group step
+  const uint32_t row_bytes = (uint32_t)(a.K * sizeof(T));
+  const T sc = (T)(a.dt * a.c_red), sd = (T)a.dt;
+  T acc[JG][APL];
+  const T *lane[JG], *single[JG];
+#pragma unroll
+  for (int j = 0; j < JG; ++j) {
+    lane[j] = Iin + j * slab + ang.k[0];
+    single[j] = Iin + j * slab + k_single;
+    ang.read_lane(ang.lane_row(lane[j], (uint32_t)cell, row_bytes), ang.lane_row(single[j], (uint32_t)cell, row_bytes),
+                  Is[j]);
+#pragma unroll
+    for (int q = 0; q < APL; ++q) acc[j][q] = T(0);
+  }
+  for (int h = 0; h < nh; h += U) {
+    uint32_t n[U];
+    V4 r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool v = h + u < nh;
+      const int i = v ? h + u : 0;
+      n[u] = (uint32_t)nbr[i];
+      r[u] = an[i];
+      if (!v) r[u] = V4{T(0), T(0), T(0), T(0)};
+    }
+    T xn[U][JG][APL];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < JG; ++j)
+        ang.read_lane(ang.lane_row(lane[j], n[u], row_bytes), ang.lane_row(single[j], n[u], row_bytes), xn[u][j]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      // the face speeds of the upwind step, and for every group its charge
+      const T ax = sc * r[u].x, ay = sc * r[u].y, az = sc * r[u].z, nb = -(sd * r[u].w);
+      const T m2b = nb + nb;
+#pragma unroll
+      for (int q = 0; q < P; ++q) {
+        const T g = fma(az, ang.z[q], fma(ay, ang.y[q], fma(ax, ang.x[q], nb)));
+        const T g2 = m2b - g;
+#pragma unroll
+        for (int j = 0; j < JG; ++j) {
+          acc[j][q] -= g * (g > T(0) ? Is[j][q] : xn[u][j][q]);
+          if (PAIRED) acc[j][q + P] -= g2 * (g2 > T(0) ? Is[j][q + P] : xn[u][j][q + P]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < JG; ++j)
+#pragma unroll
+    for (int q = 0; q < APL; ++q) Is[j][q] = Is[j][q] * cr + acc[j][q] * ci;
+}
+
 // Implicit source update (section 2.3, the four-step algorithm) of the cell `cell`,
 // whose LPC lanes hold the transported intensities Ic of their angles (updated in
 // place).  Gas energy and momentum are written by lane 0 when a.write_gas is set.
