@@ -22,7 +22,7 @@ namespace {
 // are gathered two faces per batch, all loads of a batch issued before any is used.
 // Output: the limited gradient as [N][3][K] (PACKED false), or, for the PLM step's own
 // stage 2, each cell and angle's face state (phi, alpha grad phi) in 16-byte parts (PACKED
-// true).  Bound by the address units of its gathers (FP64 64^3 x 80: 0.29 of 0.39 ms) and the
+// true; with split = K/2 the states of angles 0, 2, 4, ... first, then those of 1, 3, 5, ...).  Bound by the address units of its gathers (FP64 64^3 x 80: 0.29 of 0.39 ms) and the
 // bytes of its output; in a full layout (K = LPC APL) a neighbour's elements sit at compile-time
 // offsets from one 64-bit multiply-add per face (two PLM steps at 64^3 x 80, FP64 2.63 -> 2.54
 // ms).  Two or four consecutive angles per lane (fewer, wider gathers) spread its stores over
@@ -33,7 +33,7 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
                                                        const void *hf_rel, const void *cell_gb,
                                                        const double *__restrict__ vol0,
                                                        const T *__restrict__ I, T *__restrict__ G, int hf_cap,
-                                                       int64_t nblk, bool past_caches) {
+                                                       int64_t nblk, int split, bool past_caches) {
   using V4 = typename rt_vec4<T>::type;
   constexpr int U = 2;
   constexpr int CPB = RT_BLOCK / LPC;
@@ -135,7 +135,8 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
     const int k = kk[q];
     if constexpr (PACKED) {
       using S = rt_state<T>;
-      typename S::part *o = (typename S::part *)G + S::PARTS * cell * K + k;
+      const int at = split ? (k >> 1) + (k & 1 ? split : 0) : k;
+      typename S::part *o = (typename S::part *)G + S::PARTS * cell * K + at;
       if (FULL && past_caches) S::template store<true>(o, K, s[q], al * gx[q], al * gy[q], al * gz[q]);
       else S::template store<false>(o, K, s[q], al * gx[q], al * gy[q], al * gz[q]);
     } else {
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
 }
 
 template <typename T, int LPC, int APL, bool FULL, bool PACKED>
-hipError_t launch_one(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s) {
+hipError_t launch_one(const rt_mesh *m, int K, const void *I, void *G, int split, hipStream_t s) {
   using V4 = typename rt_vec4<T>::type;
   const int64_t cpb = RT_BLOCK / LPC;
   const int64_t nblk = (m->N + cpb - 1) / cpb;
@@ -164,27 +165,27 @@ hipError_t launch_one(const rt_mesh *m, int K, const void *I, void *G, hipStream
   const bool past_caches = PACKED && (int64_t)sizeof(V4) * m->N * K > (int64_t)128 << 20;
   hipLaunchKernelGGL((k_gradient<T, LPC, APL, FULL, PACKED>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK), smem,
                      s, m->N, K, m->row_ptr, m->hf_nbr, gp, rel, gb, m->vol0, (const T *)I, (T *)G, cap, nblk,
-                     past_caches);
+                     split, past_caches);
   return hipGetLastError();
 }
 
 template <typename T, int LPC, int APL, bool PACKED>
-hipError_t launch(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s) {
-  return K == LPC * APL ? launch_one<T, LPC, APL, true, PACKED>(m, K, I, G, s)
-                        : launch_one<T, LPC, APL, false, PACKED>(m, K, I, G, s);
+hipError_t launch(const rt_mesh *m, int K, const void *I, void *G, int split, hipStream_t s) {
+  return K == LPC * APL ? launch_one<T, LPC, APL, true, PACKED>(m, K, I, G, split, s)
+                        : launch_one<T, LPC, APL, false, PACKED>(m, K, I, G, split, s);
 }
 
 template <typename T, bool PACKED>
-hipError_t dispatch16(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s) {
+hipError_t dispatch16(const rt_mesh *m, int K, const void *I, void *G, int split, hipStream_t s) {
   switch ((K + 15) / 16) {
-    case 1: return launch<T, 16, 1, PACKED>(m, K, I, G, s);
-    case 2: return launch<T, 16, 2, PACKED>(m, K, I, G, s);
-    case 3: return launch<T, 16, 3, PACKED>(m, K, I, G, s);
-    case 4: return launch<T, 16, 4, PACKED>(m, K, I, G, s);
-    case 5: return launch<T, 16, 5, PACKED>(m, K, I, G, s);
-    case 6: return launch<T, 16, 6, PACKED>(m, K, I, G, s);
-    case 7: return launch<T, 16, 7, PACKED>(m, K, I, G, s);
-    case 8: return launch<T, 16, 8, PACKED>(m, K, I, G, s);
+    case 1: return launch<T, 16, 1, PACKED>(m, K, I, G, split, s);
+    case 2: return launch<T, 16, 2, PACKED>(m, K, I, G, split, s);
+    case 3: return launch<T, 16, 3, PACKED>(m, K, I, G, split, s);
+    case 4: return launch<T, 16, 4, PACKED>(m, K, I, G, split, s);
+    case 5: return launch<T, 16, 5, PACKED>(m, K, I, G, split, s);
+    case 6: return launch<T, 16, 6, PACKED>(m, K, I, G, split, s);
+    case 7: return launch<T, 16, 7, PACKED>(m, K, I, G, split, s);
+    case 8: return launch<T, 16, 8, PACKED>(m, K, I, G, split, s);
   }
   return hipErrorInvalidValue;
 }
@@ -192,27 +193,28 @@ hipError_t dispatch16(const rt_mesh *m, int K, const void *I, void *G, hipStream
 // Small angle sets take 8 lanes per cell (32-cell workgroups); if their half-face
 // records do not fit in LDS, 16 lanes (16-cell workgroups) halve the staging.
 template <typename T, bool PACKED>
-hipError_t dispatch(const rt_mesh *m, int K, const void *I, void *G, hipStream_t s) {
-  if (K % 16 == 0 || K > 64) return dispatch16<T, PACKED>(m, K, I, G, s);
+hipError_t dispatch(const rt_mesh *m, int K, const void *I, void *G, int split, hipStream_t s) {
+  if (K % 16 == 0 || K > 64) return dispatch16<T, PACKED>(m, K, I, G, split, s);
   hipError_t e = hipErrorInvalidValue;
   switch ((K + 7) / 8) {
-    case 1: e = launch<T, 8, 1, PACKED>(m, K, I, G, s); break;
-    case 2: e = launch<T, 8, 2, PACKED>(m, K, I, G, s); break;
-    case 3: e = launch<T, 8, 3, PACKED>(m, K, I, G, s); break;
-    case 4: e = launch<T, 8, 4, PACKED>(m, K, I, G, s); break;
-    case 5: e = launch<T, 8, 5, PACKED>(m, K, I, G, s); break;
-    case 6: e = launch<T, 8, 6, PACKED>(m, K, I, G, s); break;
-    case 7: e = launch<T, 8, 7, PACKED>(m, K, I, G, s); break;
-    case 8: e = launch<T, 8, 8, PACKED>(m, K, I, G, s); break;
+    case 1: e = launch<T, 8, 1, PACKED>(m, K, I, G, split, s); break;
+    case 2: e = launch<T, 8, 2, PACKED>(m, K, I, G, split, s); break;
+    case 3: e = launch<T, 8, 3, PACKED>(m, K, I, G, split, s); break;
+    case 4: e = launch<T, 8, 4, PACKED>(m, K, I, G, split, s); break;
+    case 5: e = launch<T, 8, 5, PACKED>(m, K, I, G, split, s); break;
+    case 6: e = launch<T, 8, 6, PACKED>(m, K, I, G, split, s); break;
+    case 7: e = launch<T, 8, 7, PACKED>(m, K, I, G, split, s); break;
+    case 8: e = launch<T, 8, 8, PACKED>(m, K, I, G, split, s); break;
   }
-  return e == hipErrorInvalidConfiguration ? dispatch16<T, PACKED>(m, K, I, G, s) : e;
+  return e == hipErrorInvalidConfiguration ? dispatch16<T, PACKED>(m, K, I, G, split, s) : e;
 }
 
 }  // namespace
 
-hipError_t rt_launch_gradient(const rt_mesh *m, int K, const void *I, void *grad, int dtype, bool packed,
+hipError_t rt_launch_gradient(const rt_mesh *m, int K, const void *I, void *grad, int dtype, bool packed, int split,
                               hipStream_t s) {
   if (packed)
-    return dtype == RT_F32 ? dispatch<float, true>(m, K, I, grad, s) : dispatch<double, true>(m, K, I, grad, s);
-  return dtype == RT_F32 ? dispatch<float, false>(m, K, I, grad, s) : dispatch<double, false>(m, K, I, grad, s);
+    return dtype == RT_F32 ? dispatch<float, true>(m, K, I, grad, split, s)
+                           : dispatch<double, true>(m, K, I, grad, split, s);
+  return dtype == RT_F32 ? dispatch<float, false>(m, K, I, grad, 0, s) : dispatch<double, false>(m, K, I, grad, 0, s);
 }

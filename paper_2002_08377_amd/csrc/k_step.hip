@@ -170,15 +170,19 @@ k_step(rt_step_args a, int64_t nblk) {
       // state per pair is gathered, chosen by the sign of the face speed, and the second where
       // both enter.  The kernel is bound by the address and data units of its gathers (80% of the
       // time, both precisions) and the L2 lines behind them: 64^3 x 80 step with antipodes K/2
-      // apart, FP64 1.64 -> 1.28 ms, side by side (the pair shares its lines) 1.38 -> 1.28;
-      // FP32 0.74 -> 0.69 and 0.71 -> 0.67.  Faces at a third of the light speed, where many
-      // pairs enter whole: FP32 0.326 -> 0.331 ms (48^3 x 80), FP64 0.72 -> 0.61.
+      // apart, FP64 1.64 -> 1.25 ms, side by side 1.38 -> 1.24; FP32 0.74 -> 0.69 and 0.71 -> 0.65.
+      // Faces at a third of the light speed, where many pairs enter whole: FP32 0.323 -> 0.324 ms
+      // (48^3 x 80), FP64 0.72 -> 0.61.  Up to 20^3 cells, where a CU has one workgroup and waits
+      // for each face in turn, the choice lengthens the FP32 chain (12^3 x 80: 41.2 -> 42.5 us).
       using S = rt_state<T>;
       const int KK = FULL ? LPC * APL : K;
-      const typename S::part *states = (const typename S::part *)a.states + ang.k[0];
+      // a pair's states are K/2 apart in either order of the angles, so that lanes which pick the
+      // same side read whole lines (two PLM steps with antipodes side by side, their states beside
+      // each other: FP32 1.370 -> 1.344 ms, FP64 2.574 -> 2.504)
+      const typename S::part *states = (const typename S::part *)a.states + (PAIRED ? l : ang.k[0]);
       const uint32_t state_row = (uint32_t)(K * sizeof(V4));
       auto of = [&](uint32_t c) { return (const typename S::part *)((const char *)states + (uint64_t)c * state_row); };
-      auto at = [&](int q) { return FULL ? Ang::slot_offset(q) : ang.k[q] - ang.k[0]; };
+      auto at = [&](int q) { return FULL ? LPC * q : ang.k[q] - ang.k[0]; };
       V4 own[APL];
 #pragma unroll
       for (int q = 0; q < APL; ++q) own[q] = S::load(of((uint32_t)cell) + at(q), KK);
@@ -207,7 +211,7 @@ k_step(rt_step_args a, int64_t nblk) {
         V4 x[UP][P];
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
-          const typename S::part *n = of(j[u]), *anti = PAIRED ? n + (PAIRED == 2 ? 1 : LPC * P) : n;
+          const typename S::part *n = of(j[u]), *anti = n + LPC * P;
 #pragma unroll
           for (int q = 0; q < P; ++q) x[u][q] = S::load((PAIRED && !(g[u][q] < T(0)) ? anti : n) + at(q), KK);
         }
@@ -220,11 +224,12 @@ k_step(rt_step_args a, int64_t nblk) {
 #pragma unroll
           for (int q = 0; q < P; ++q) {
             const T n = there(x[u][q]);
-            acc[q] -= g[u][q] * (g[u][q] > T(0) ? here(own[q]) : n);
+            const bool in = g[u][q] < T(0);
+            acc[q] -= g[u][q] * (in ? n : here(own[q]));
             if (PAIRED) {
               const T g2 = m2b[u] - g[u][q];  // the antipodal angle, as in the upwind loop
-              const bool both = g[u][q] < T(0) && g2 < T(0);
-              const T to = acc[q + P] - g2 * (g2 > T(0) ? here(own[q + P]) : n);
+              const bool in2 = g2 < T(0), both = in && in2;
+              const T to = acc[q + P] - g2 * (in2 ? n : here(own[q + P]));
               acc[q + P] = both ? acc[q + P] : to;
               more |= both;
             }
@@ -279,6 +284,11 @@ k_step(rt_step_args a, int64_t nblk) {
   if (MODE == 1 && l == 0 && a.src_tape_out) a.src_tape_out[RT_SRC_TAPE * cell + RT_TAPE_V] = Vstart;
 }
 
+size_t rt_step_lds(int mode, size_t v4, int hf_cap) {
+  const bool faces = mode >= 1 && mode <= 4;
+  return faces ? ((mode == 2 ? 3 : 1) * v4 + sizeof(int32_t)) * (size_t)hf_cap : 0;
+}
+
 // Staging needs (records per half-face) x (half-faces of the largest range of the
 // workgroup's cells) bytes of LDS; a layout that would need more than a workgroup may
 // use (160 KiB on gfx950) is refused with hipErrorInvalidConfiguration (the dispatch then
@@ -292,9 +302,7 @@ hipError_t launch_mode(const rt_step_args &args, hipStream_t s) {
   const int64_t cpb = RT_BLOCK / LPC;
   const int64_t nblk = (a.N + cpb - 1) / cpb;
   const dim3 grid((unsigned)rt_grid_for(nblk)), block(RT_BLOCK);
-  const size_t per = (a.do_transport == 2 ? 3 : 1) * sizeof(V4) + sizeof(int32_t);
-  const bool faces = a.do_transport >= 1 && a.do_transport <= 4;
-  const size_t smem = faces ? per * (size_t)a.hf_cap : 0;
+  const size_t smem = rt_step_lds(a.do_transport, sizeof(V4), a.hf_cap);
   if (smem > (size_t)a.lds_max) return hipErrorInvalidConfiguration;
   switch (a.do_transport) {
     case 0: hipLaunchKernelGGL((k_step<T, LPC, APL, 0, FULL, PAIRED>), grid, block, smem, s, a, nblk); break;
@@ -372,6 +380,12 @@ template <typename T> hipError_t dispatch(const rt_step_args &a, hipStream_t s) 
 }
 
 }  // namespace
+
+bool rt_plm_pairs(const rt_step_args &a, int dtype) {
+  const int lanes = a.paired ? rt_paired_lanes(a.K) : 0;
+  const size_t v4 = dtype == RT_F32 ? sizeof(float4) : sizeof(double4);
+  return lanes && rt_step_lds(2, v4, (lanes >> 8) == 8 ? a.hf_cap32 : a.hf_cap64) <= (size_t)a.lds_max;
+}
 
 hipError_t rt_launch_step(const rt_step_args &a, int dtype, hipStream_t s) {
   return dtype == RT_F32 ? dispatch<float>(a, s) : dispatch<double>(a, s);

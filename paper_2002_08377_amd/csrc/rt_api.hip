@@ -208,9 +208,6 @@ int run_step(rt_mesh *m, const rt_params *p, const rt_angles *a, const void *I_i
   s1.write_gas = 0;
   hipError_t e = rt_launch_step(s1, p->dtype, st);
   if (e != hipSuccess) return hip_fail(e, "stage-1 kernel launch");
-  // (I_half, gradient) packed per cell and angle for stage 2
-  e = rt_launch_gradient(m, a->K, m->I_half, m->states, p->dtype, true, st);
-  if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
   // stage 2: reconstructed fluxes of the half-step state on the start-of-step charges, source on gas^n
   rt_step_args s2 = s;
   s2.I_in = I_in;
@@ -222,6 +219,10 @@ int run_step(rt_mesh *m, const rt_params *p, const rt_angles *a, const void *I_i
   s2.do_transport = 2;
   s2.do_source = src;
   s2.write_gas = 1;
+  // (I_half, gradient) packed per cell and angle for stage 2
+  e = rt_launch_gradient(m, a->K, m->I_half, m->states, p->dtype, true,
+                         s2.paired == 2 && rt_plm_pairs(s2, p->dtype) ? a->K / 2 : 0, st);
+  if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
   e = rt_launch_step(s2, p->dtype, st);
   if (e != hipSuccess) return hip_fail(e, "stage-2 kernel launch");
   return RT_OK;
@@ -615,7 +616,7 @@ int rt_gradient(rt_mesh *m, const rt_params *p, const rt_angles *a, const void *
   if (rc) return rc;
   if ((rc = check_ptrs({I, grad}))) return rc;
   if (!(m->flags & RT_MESH_PLM)) return fail(RT_ESTATE, "rt_gradient needs a mesh uploaded with RT_MESH_PLM");
-  hipError_t e = rt_launch_gradient(m, a->K, I, grad, p->dtype, false, (hipStream_t)stream);
+  hipError_t e = rt_launch_gradient(m, a->K, I, grad, p->dtype, false, 0, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
   return RT_OK;
 }

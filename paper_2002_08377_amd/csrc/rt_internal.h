@@ -144,7 +144,11 @@ static inline int rt_step_lanes(int K, int paired) {
 }
 
 hipError_t rt_launch_step(const rt_step_args &a, int dtype, hipStream_t s);
-hipError_t rt_launch_gradient(const rt_mesh *m, int K, const void *I, void *grad, int dtype, bool packed,
+// whether the PLM stage 2 `a` describes runs in a paired layout (else in the general one)
+bool rt_plm_pairs(const rt_step_args &a, int dtype);
+// packed: face states instead of gradients, in the order of the angles, or (split = K/2, antipodes
+// side by side) each pair's first angles, then their antipodes
+hipError_t rt_launch_gradient(const rt_mesh *m, int K, const void *I, void *grad, int dtype, bool packed, int split,
                               hipStream_t s);
 
 struct rt_adj_args {
