@@ -36,11 +36,10 @@ template <typename T, int APL, int PAIRED> struct rt_batch {
 // The cells of a workgroup are consecutive, so their half-faces form one contiguous
 // range; it is staged in LDS (dynamic size: the largest range of any workgroup,
 // found at upload) and the face loops read their records from there.
-// Occupancy target: the FP64 PLM stage 2 takes 252 registers and the FP64 source reverse would
-// take 262, one wave per SIMD; both are held to two (the reverse spills five registers then).
-// Everything else keeps the compiler's choice.
+// Occupancy target: the FP64 PLM stage 2 takes 252 registers, two waves per SIMD, and is held
+// to that.  Everything else keeps the compiler's choice.
 template <typename T, int MODE> struct rt_step_waves {
-  static constexpr int value = sizeof(T) == 8 && (MODE == 2 || MODE >= 4) ? 2 : 1;
+  static constexpr int value = MODE == 2 && sizeof(T) == 8 ? 2 : 1;
 };
 template <typename T, int LPC, int APL, int MODE, bool FULL, int PAIRED>
 __global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_step_waves<T, MODE>::value))) void

@@ -49,56 +49,66 @@ __device__ __forceinline__ void rt_source_vjp_cell(const rt_step_args &a, const 
   const double Aq = dt * c * rho * kP * a.a_rad * S1 * iD;
 
   const T tg = (T)gam, tvx = (T)(vx * ic), tvy = (T)(vy * ic), tvz = (T)(vz * ic);
-  const T ychiA = (T)(y * chi), ySA = (T)(y * Ssrc), iQA = (T)iQ;
+  const T yA = (T)y, ychiA = (T)(y * chi), SsA = (T)Ssrc, iQA = (T)iQ;
   // the gas bookkeeping hands I* - I' to the gas: the energy and momentum adjoints reach
   // each angle as 4 pi W (c lamE + n.lamM) / cbar
   const double lEp = a.lamE[cell];
   const double lmp0 = a.lamM[3 * cell], lmp1 = a.lamM[3 * cell + 1], lmp2 = a.lamM[3 * cell + 2];
   const T clE = (T)(c * lEp), lm0 = (T)lmp0, lm1 = (T)lmp1, lm2 = (T)lmp2, mg = (T)a.m_gain;
 
-  // The reverse is bound by vector issue behind the transpose of transport, at the three waves
-  // per SIMD its kept values leave, so the three passes over the angles are written in what
-  // survives of the forward quantities (FP32, 80 angles: 1566 -> 1276 instructions; gradient of
-  // 16 steps at 96^3 x 80 in FP32 23.2 -> 22.8 ms, of 20 steps at 32^3 x 48 in FP64 1.21 ->
-  // 1.18 ms; held to four waves it spills 45 registers and takes 28.5 ms).  With X = I' Gamma^4 / r
-  // and R0 = r Gamma^4 I* = I' Gamma^4 - y S Gamma r:
-  //   ell = dL/dI' net of the bookkeeping,  dL/dS = y sum ell r Gamma^-3,
-  //   zr = r (lS1 + lSG Gamma + lSI Gamma^4 I*) = r (lS1 + lSG Gamma) + lSI R0    (dL/dWt),
-  //   dL/d(1/r) = -(ell I' r + zr Wt r),
-  //   dL/dGamma = -3 y S ell r Gamma^-4 + Wt (lSG r + (4 lSI R0 - 2 (zr - sum zr Wt)) / Gamma)
-  //               + y chi dL/d(1/r),
-  //   dL/dI* = bookkeeping + r (ell + lSI W Gamma^2 / sum W Gamma^-2),
-  // where the two terms -+4 ell I' / Gamma of dL/dGamma have cancelled exactly.  R0 itself
-  // cancels where a cell is optically thick, to the rounding of I' (as the forward's own r
-  // scales every use of Gamma^4 I*).
-  // Between the passes a lane keeps only I', ell, gamma v.n / c per direction, and 1 / Gamma
-  // and r per slot; each pass rebuilds the other quantities from them.  Empty register
+  // Between the passes a lane keeps only I', the adjoint (dL/dI' net of the bookkeeping
+  // after the first pass, dL/dI* at the end), v.n / c per direction, and 1 / Gamma and r
+  // per slot; each pass rebuilds the other forward quantities from them.  Empty register
   // barriers on the kept values make the rebuild real: without them the compiler holds
-  // every intermediate across the group sums, at the cost of a wave per SIMD.
+  // every intermediate across the group sums.  At 96^3 x 80 with antipodes side by side
+  // (transpose of transport fused in front): FP32 222 registers per lane, two waves per
+  // SIMD, 0.83 ms per launch; with the barriers 160 registers, three waves, 0.65 ms (FP64
+  // 350 -> 256 registers, 1.64 -> 1.08 ms).  Forcing a fourth FP32 wave spills: 0.71 ms.
+  struct Fw {
+    T G, iG, iG2, iG4, r, I0, X;
+  };
+  T iGk[APL], rk[APL];  // 1 / Gamma and r per slot, kept from the first pass
+  auto fw = [&](int s, T vn, bool first) {  // slot s, v.n / c along the slot's own direction
+    Fw f;
+    f.G = tg * (T(1) - vn);
+    f.iG = first ? rt_rcp(f.G) : iGk[s];
+    f.iG2 = f.iG * f.iG;
+    f.iG4 = f.iG2 * f.iG2;
+    const T den = T(1) + ychiA * f.G;  // 1 / r
+    f.r = first ? rt_rcp(den) : rk[s];
+    iGk[s] = f.iG;
+    rk[s] = f.r;
+    const T G2 = f.G * f.G;
+    // X = Gamma^4 I* + y Gamma S from the step's output I' = X r / Gamma^4; Gamma^4 I* = X - y
+    // Gamma S cancels where the cell is optically thick (r << 1), but every use of it below is
+    // scaled by r again, so its absolute error stays at the rounding of I'
+    f.X = Io[s] * (G2 * G2) * den;
+    f.I0 = f.X - yA * f.G * SsA;
+    return f;
+  };
+  auto through = [&](int s, T nl) { return (T)ang.wt(s) * mg * (clE + nl); };
   constexpr int H = PAIRED ? 2 : 1;  // slots per stored direction
-  T gv[P], iGk[APL], rk[APL];
-  auto gamma = [&](int q, int h) { return h ? tg + gv[q] : tg - gv[q]; };  // the antipode has direction -n
-  auto through = [&](int q, int h, T nl) { return (T)ang.wt(q) * mg * (h ? clE - nl : clE + nl); };
+  T vnp[P];
 
   // ---- first pass: dL/dI' net of the bookkeeping, and dL/dS ------------------------------
   double lS = 0.0;
 #pragma unroll
   for (int q = 0; q < P; ++q) {
-    gv[q] = tg * (tvx * ang.dx(q) + tvy * ang.dy(q) + tvz * ang.dz(q));
+    const T vn = tvx * ang.dx(q) + tvy * ang.dy(q) + tvz * ang.dz(q);
     const T nl = ang.dx(q) * lm0 + ang.dy(q) * lm1 + ang.dz(q) * lm2;
+    vnp[q] = vn;
 #pragma unroll
     for (int h = 0; h < H; ++h) {
       const int s = q + h * P;
-      const T G = gamma(q, h);
-      iGk[s] = rt_rcp(G);
-      rk[s] = rt_rcp(T(1) + ychiA * G);
+      const Fw f = fw(s, h ? -vn : vn, true);  // the antipode has direction -n
       // a slot past K (general layout) holds no angle: its weight is zero, and so must be
       // its adjoint, whatever the slot's row entry holds
-      lam[s] = (ang.ok[s] ? lam[s] : T(0)) - through(q, h, nl);
-      lS += (double)(lam[s] * rk[s] * (iGk[s] * iGk[s] * iGk[s]));
+      const T ell = (ang.ok[s] ? lam[s] : T(0)) - through(s, h ? -nl : nl);
+      lam[s] = ell;
+      lS += (double)(ell * f.iG4 * yA * f.G * f.r);
     }
   }
-  lS = y * rt_group_sum<LPC>(lS);
+  lS = rt_group_sum<LPC>(lS);
 
   // ---- per cell: S -> J, T -> the root's A and C -> the sums, kappas, gas state ----------
   double lkP = lS * planck, lkJ = 0.0;
@@ -126,26 +136,24 @@ __device__ __forceinline__ void rt_source_vjp_cell(const rt_step_args &a, const 
   lSG += lD * y * kJ;
   const T lS1A = (T)lS1, lSGA = (T)lSG, lSIA = (T)lSI;
 
-  // per slot: R0, Wt, zr and -dL/d(1/r)
+  // The adjoints of the sums' weights Wt and of r = 1 / (1 + y chi Gamma), per slot, from
+  // the first pass's dL/dI' (ell): dL/d(X r) = ell Gamma^-4, dL/dr = that X plus the sums'.
   struct Bw {
-    T G, R0, Wt, zr, lden;
+    T Wt, lWt, lden;
   };
-  auto bw = [&](int q, int h) {
-    const int s = q + h * P;
-    const T r = rk[s], iG = iGk[s];
+  auto bw = [&](int s, const Fw &f, T ell) {
     Bw b;
-    b.G = gamma(q, h);
-    const T G2 = b.G * b.G;
-    b.R0 = Io[s] * (G2 * G2) - ySA * b.G * r;
-    b.Wt = (T)ang.wt(q) * iQA * (iG * iG);
-    b.zr = r * (lS1A + lSGA * b.G) + lSIA * b.R0;
-    b.lden = lam[s] * Io[s] * r + b.zr * b.Wt * r;
+    b.Wt = (T)ang.wt(s) * f.iG2 * iQA;
+    const T Z = lS1A + lSGA * f.G + lSIA * f.I0;
+    b.lWt = Z * f.r;
+    const T lr = ell * f.iG4 * f.X + Z * b.Wt;
+    b.lden = -lr * f.r * f.r;
     return b;
   };
 
   // ---- second pass: dL/dchi through r and the weights' normalisation ---------------------
 #pragma unroll
-  for (int q = 0; q < P; ++q) asm volatile("" : "+v"(gv[q]));
+  for (int q = 0; q < P; ++q) asm volatile("" : "+v"(vnp[q]));
 #pragma unroll
   for (int q = 0; q < APL; ++q) asm volatile("" : "+v"(iGk[q]), "+v"(rk[q]));
   double lchi = 0.0, sw = 0.0;
@@ -153,47 +161,54 @@ __device__ __forceinline__ void rt_source_vjp_cell(const rt_step_args &a, const 
   for (int q = 0; q < P; ++q) {
 #pragma unroll
     for (int h = 0; h < H; ++h) {
-      const Bw b = bw(q, h);
-      lchi += (double)(b.lden * b.G);
-      sw += (double)(b.zr * b.Wt);
+      const int s = q + h * P;
+      const Fw f = fw(s, h ? -vnp[q] : vnp[q], false);
+      const Bw b = bw(s, f, lam[s]);
+      lchi += (double)(b.lden * yA * f.G);
+      sw += (double)(b.lWt * b.Wt);
     }
   }
-  lchi = -y * rt_group_sum<LPC>(lchi);
+  lchi = rt_group_sum<LPC>(lchi);
   sw = rt_group_sum<LPC>(sw);
   lkJ += lchi;
 
-  // ---- third pass: Gamma through gamma and v, and dL/dI* ----------------------------------
+  // ---- third pass: Wt through Gamma^-2, I0 = Gamma^4 I*, Gamma through gamma and v --------
 #pragma unroll
-  for (int q = 0; q < P; ++q) asm volatile("" : "+v"(gv[q]));
+  for (int q = 0; q < P; ++q) asm volatile("" : "+v"(vnp[q]));
 #pragma unroll
   for (int q = 0; q < APL; ++q) asm volatile("" : "+v"(iGk[q]), "+v"(rk[q]));
-  const T swA = (T)sw, y3S = T(3) * ySA, lSI4 = T(4) * lSIA;
+  const T swA = (T)sw, igamA = (T)(1.0 / gam), glc = (T)(gam * ic);
   double lgam = 0.0, lvx = 0.0, lvy = 0.0, lvz = 0.0;
 #pragma unroll
   for (int q = 0; q < P; ++q) {
     const T nl = ang.dx(q) * lm0 + ang.dy(q) * lm1 + ang.dz(q) * lm2;
-    double gs = 0.0;  // sum of -+dL/dGamma over the slots
+    double gs = 0.0;  // sum of dL/dGamma * dGamma/d(v.n) along +n over the slots
 #pragma unroll
     for (int h = 0; h < H; ++h) {
       const int s = q + h * P;
-      const Bw b = bw(q, h);
-      const T ell = lam[s], r = rk[s], iG = iGk[s], iG2 = iG * iG;
-      const T lg = b.Wt * (lSGA * r + iG * (lSI4 * b.R0 - T(2) * (b.zr - swA))) - y3S * (ell * r * (iG2 * iG2)) -
-                   ychiA * b.lden;
-      lam[s] = through(q, h, nl) + r * (ell + lSIA * ((T)ang.wt(q) * iQA * (b.G * b.G)));
-      lgam += (double)(lg * b.G);
-      gs += (double)(h == 0 ? -lg : lg);
+      const Fw f = fw(s, h ? -vnp[q] : vnp[q], false);
+      const T ell = lam[s];
+      const Bw b = bw(s, f, ell);
+      const T lIn = ell * f.iG4;
+      const T lIco = lIn * f.r + lSIA * b.Wt * f.r;
+      const T lq = (b.lWt - swA) * iQA;
+      const T qv = (T)ang.wt(s) * f.iG2;  // W Gamma^-2, the sums' unnormalised weight
+      const T lg = T(-4) * ell * f.X * f.r * f.iG4 * f.iG + lIn * yA * SsA * f.r + lSGA * b.Wt * f.r +
+                   b.lden * ychiA + lq * (T(-2) * qv * f.iG) + lIco * T(4) * f.I0 * f.iG;
+      const T G2 = f.G * f.G;
+      lam[s] = through(s, h ? -nl : nl) + lIco * G2 * G2;
+      lgam += (double)(lg * f.G * igamA);
+      // Gamma = gamma (1 -+ v.n / c): dGamma/dv = -+ gamma n / c
+      gs += (double)(h == 0 ? -(lg * glc) : lg * glc);
     }
     lvx += gs * (double)ang.dx(q);
     lvy += gs * (double)ang.dy(q);
     lvz += gs * (double)ang.dz(q);
   }
-  // Gamma = gamma (1 -+ v.n / c): dGamma/dgamma = Gamma / gamma, dGamma/dv = -+ gamma n / c
-  const double glc = gam * ic;
-  lgam = rt_group_sum<LPC>(lgam) * rt_rcp(gam);
-  lvx = rt_group_sum<LPC>(lvx) * glc;
-  lvy = rt_group_sum<LPC>(lvy) * glc;
-  lvz = rt_group_sum<LPC>(lvz) * glc;
+  lgam = rt_group_sum<LPC>(lgam);
+  lvx = rt_group_sum<LPC>(lvx);
+  lvy = rt_group_sum<LPC>(lvy);
+  lvz = rt_group_sum<LPC>(lvz);
   const T iVp = (T)rt_rcp(Vp);
 #pragma unroll
   for (int q = 0; q < APL; ++q) lam[q] *= iVp;
