@@ -380,6 +380,8 @@ int rt_step_mg(rt_mesh *mesh, const rt_params *params, const rt_angles *angles, 
  * of at most 1e-14 T, which is taken as it is, or to one of at most 1e-8 T
  * after which the next, by the last two, would be at most 2e-17 T.  Where f has several roots this gives the one reached from
  * T^n.  With bP = bJ = 0 it gives the root of rt_source_implicit's quartic.
+ * A cell whose gas energy is below its kinetic energy has no temperature: its
+ * intensities, momentum and energy become NaN, which rt_diagnostics counts.
  * Per-angle arithmetic is FP64 in both precision forms.  Other arguments as
  * rt_source_implicit.
  */

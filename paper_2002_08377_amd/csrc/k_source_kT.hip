@@ -93,7 +93,12 @@ __device__ __forceinline__ void rt_kT_cell(const rt_kT_args &a, const double *s_
   const double rcv = rho * a.cv;
   const double Tn = (Eg - 0.5 * (m0 * m0 + m1 * m1 + m2 * m2) * irho) * rt_rcp(rcv);
   const double iTref = rt_rcp(a.T_ref);
-  const double kP0 = a.kP0[cell], kJ0 = a.kJ0[cell], ks = a.ks[cell];
+  const double kJ0 = a.kJ0[cell], ks = a.ks[cell];
+  // Gas with less total than kinetic energy has no temperature.  The logarithm makes such a cell
+  // NaN, which the diagnostics count; multiplication would not (x^2 of a negative x is as good as
+  // any), so there the opacity is made NaN here.  At T = 0 only two rising laws have a value.
+  const bool cold = HALF && (Tn < 0.0 || (Tn == 0.0 && (a.bP2 <= 0 || a.bJ2 <= 0)));
+  const double kP0 = cold ? NAN : a.kP0[cell];
 
   auto evaluate = [&](double Tq) {
     kT_eval e;
