@@ -52,10 +52,10 @@ k_step(rt_step_args a, int64_t nblk) {
   using Ang = rt_step_angles<T, LPC, APL, FULL, PAIRED, MODE != 2>;
   constexpr bool FACES = MODE >= 1 && MODE <= 4;  // the modes that read face records
   constexpr bool TRANSPOSE = MODE == 3 || MODE == 4;
-  // PLM stage 2 reads I_in and writes I_out once; past the caches, they leave those to the
-  // gathered states (64^3 x 80 step, FP64 1.343 -> 1.333 ms).  Rows of part lines stay in the
-  // caches: past them a step at 48^3 x 37 took 0.22 ms (FP32) instead of 0.20.
-  constexpr bool NT = MODE == 2 && FULL && LPC * APL * sizeof(T) % 64 == 0;
+  // PLM stage 2 reads I_in and writes I_out once; past the caches, where the launch says so, they
+  // leave those to the gathered states.  Rows of part lines stay in the caches: past them a step
+  // at 48^3 x 37 took 0.22 ms (FP32) instead of 0.20.
+  constexpr bool LINES = MODE == 2 && FULL && LPC * APL * sizeof(T) % 64 == 0;
   constexpr int P = Ang::P;
   constexpr int U = rt_batch<T, APL, PAIRED>::U;
   constexpr int CPB = RT_BLOCK / LPC;
@@ -98,7 +98,8 @@ k_step(rt_step_args a, int64_t nblk) {
   const int k_single = Ang::SINGLE ? ang.k[P - 1] : ang.k[0];
   const T *Iin_lane = Iin + ang.k[0], *Iin_single = Iin + k_single;
   T Ic[APL];
-  ang.template read_lane<NT>(Iin_lane + row, Iin_single + row, Ic);
+  if (LINES && a.past_caches) ang.template read_lane<true>(Iin_lane + row, Iin_single + row, Ic);
+  else ang.read_lane(Iin_lane + row, Iin_single + row, Ic);
 
   double Vnew = 0.0, Vstart = 0.0;
   // the start-of-step volume: the reverse modes take it from the forward step's tape
@@ -277,7 +278,8 @@ k_step(rt_step_args a, int64_t nblk) {
 
   {
     T *o = (T *)a.I_out + row;
-    ang.template write_lane<NT>(o + ang.k[0], o + k_single, Ic);
+    if (LINES && a.past_caches) ang.template write_lane<true>(o + ang.k[0], o + k_single, Ic);
+    else ang.write_lane(o + ang.k[0], o + k_single, Ic);
   }
   if ((MODE == 1 || MODE == 2) && l == 0 && a.vol_out) a.vol_out[cell] = Vnew;
   if (MODE == 1 && l == 0 && a.src_tape_out) a.src_tape_out[RT_SRC_TAPE * cell + RT_TAPE_V] = Vstart;
@@ -301,6 +303,11 @@ hipError_t launch_mode(const rt_step_args &args, hipStream_t s) {
   const int64_t cpb = RT_BLOCK / LPC;
   const int64_t nblk = (a.N + cpb - 1) / cpb;
   const dim3 grid((unsigned)rt_grid_for(nblk)), block(RT_BLOCK);
+  // Rows that fit in the L2s (eight of 4 MB) are read back from there by the next half step, which
+  // gathers each about 16 times.  Two PLM steps, past the caches or through them: FP32 K = 80
+  // 32^3 (10 MB) 0.192 or 0.190 ms, 40^3 (20 MB) 0.315 or 0.310, 48^3 (35 MB) 0.538 or 0.549; FP64
+  // 32^3 (21 MB) 0.317 or 0.310, 48^3 (71 MB) 1.080 or 1.088, 64^3 (168 MB) 2.486 or 2.502.
+  a.past_caches = (int64_t)sizeof(T) * a.N * a.K > (int64_t)32 << 20;
   const size_t smem = rt_step_lds(a.do_transport, sizeof(V4), a.hf_cap);
   if (smem > (size_t)a.lds_max) return hipErrorInvalidConfiguration;
   switch (a.do_transport) {
