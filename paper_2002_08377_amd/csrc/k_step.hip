@@ -17,11 +17,47 @@ namespace {
 // time at 8 to 12 angles per lane (two cost a wave per SIMD: 64^3 x 80 step, FP32 0.69 against
 // 0.70 ms, FP64 1.34 against 1.72), two at 4 and 6 (one: 48^3 x 24, FP32 0.138 against 0.142),
 // four at 2 (two: 40^3 x 8, FP32 0.062 against 0.064 ms); without pairs two (one: 48^3 x 37,
-// FP32 0.196 against 0.202 ms, FP64 0.37 against 0.48).
-template <typename T, int APL, int PAIRED> struct rt_batch {
+// FP32 0.196 against 0.202 ms, FP64 0.37 against 0.48).  Grids of a few rounds wait more than they
+// gather, and take two faces in FP32 (rt_states).
+template <typename T, int APL, int PAIRED, int STATES> struct rt_batch {
   static constexpr int U = 2;
-  static constexpr int PLM = !PAIRED ? 2 : APL > 6 ? 1 : APL > 2 ? 2 : 4;
+  static constexpr int PLM = !PAIRED || STATES == 2 || (STATES == 1 && sizeof(T) == 4 && APL > 2) ? 2
+                             : APL > 6 ? 1 : APL > 2 ? 2 : 4;
 };
+
+// Which states of an antipodal pair PLM stage 2 gathers from a neighbour: 0 the one that enters,
+// and behind it the other where both do; 1 the same, the other fetched along with the first;
+// 2 both.  The fewest fetches and registers (0) are the fastest on large grids; on small ones the
+// wait for a second fetch behind the first, or for one face after the other, is longer than the
+// fetches take, the more so the more pairs enter whole.  Two PLM steps in FP32, faces at 1e-3 / 1e-2
+// of the light speed, speed relative to the kernel that gathered both states of every pair, two
+// faces at a time, before they were stored in 16-byte parts:
+//   K = 80  12^3: (0) .97 / .91 (1) 1.00 / .98 (2) 1.00 / 1.00   32^3: 1.01 / .95, 1.07 / 1.05, 1.02 / 1.02
+//           48^3: 1.09 / 1.04, 1.08 / 1.05, 1.03 / 1.03          64^3: 1.07 / 1.03, 1.06 / 1.04, 1.01 / 1.01
+//   K = 48  12^3: (0) 1.00 / .96 (1) .99 / .98 (2) 1.03 / 1.04   32^3: 1.08 / 1.07, 1.03 / 1.02, 1.02 / 1.02
+//   K = 24  12^3: (0) 1.00 / .96 (1) .99 / .98 (2) 1.03 / 1.03   64^3: 1.02 / .98, 1.01 / 1.00, 1.00 / 1.00
+// With four lanes per cell a wave holds twice the faces, and (0) nearly always fetches twice.
+// FP64 K = 80, 12^3: (0) 1.04 / .97 (1) 1.03 / .99, 24^3: 1.10 / 1.06, 1.06 / 1.05; (2) spills.
+template <typename T> constexpr int rt_states(int lpc, int apl, int64_t nblk) {
+  const int64_t per_cu = (nblk + 255) / 256;  // workgroups
+  if (sizeof(T) == 8) return (apl == 8 || apl == 10) && per_cu <= 1 ? 1 : 0;
+  if (per_cu <= (apl >= 8 ? 1 : 2)) return 2;
+  return lpc == 4 || (apl >= 8 && per_cu <= 10) ? 1 : 0;
+}
+
+// Rows (of whole lines: rows of part lines take longer past the caches, 48^3 x 37 FP32 0.22 ms
+// against 0.20) that PLM stage 2 reads and writes past the caches, to leave those to the gathered
+// states: on meshes of more than RT_PAST_CELLS cells, or with more than RT_PAST_BYTES of rows.  On
+// smaller ones the next half step, which gathers each row about 16 times, finds more of them in the
+// caches.  Two PLM steps, past the caches or through them: FP32 K = 80, 32^3 0.192 or 0.190 ms, 40^3
+// 0.315 or 0.310, 48^3 0.538 or 0.549; K = 48, 32^3 0.139 or 0.137, 40^3 0.232 or 0.226, 48^3 0.369 or
+// 0.379; FP64 K = 80, 32^3 0.317 or 0.310, 48^3 1.080 or 1.088, 64^3 2.486 or 2.502; K = 48, 40^3 0.379 or
+// 0.385.  A kernel of its own: chosen inside one, the branch cost small grids 1 to 2%.
+#define RT_PAST_CELLS 81920
+#define RT_PAST_BYTES (22 << 20)
+template <typename T, int LPC, int APL, bool FULL> constexpr bool rt_whole_lines() {
+  return FULL && LPC * APL * sizeof(T) % 64 == 0;
+}
 
 // MODE 0: source only (in place); 1: upwind transport (+ source); 2: reconstructed
 // transport of PLM stage 2 (+ source); 3: the transpose of upwind transport (the
@@ -41,7 +77,7 @@ template <typename T, int APL, int PAIRED> struct rt_batch {
 template <typename T, int MODE> struct rt_step_waves {
   static constexpr int value = MODE == 2 && sizeof(T) == 8 ? 2 : 1;
 };
-template <typename T, int LPC, int APL, int MODE, bool FULL, int PAIRED>
+template <typename T, int LPC, int APL, int MODE, bool FULL, int PAIRED, int STATES = 0, bool PAST = false>
 __global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_step_waves<T, MODE>::value))) void
 k_step(rt_step_args a, int64_t nblk) {
   using V4 = typename rt_vec4<T>::type;
@@ -52,12 +88,8 @@ k_step(rt_step_args a, int64_t nblk) {
   using Ang = rt_step_angles<T, LPC, APL, FULL, PAIRED, MODE != 2>;
   constexpr bool FACES = MODE >= 1 && MODE <= 4;  // the modes that read face records
   constexpr bool TRANSPOSE = MODE == 3 || MODE == 4;
-  // PLM stage 2 reads I_in and writes I_out once; past the caches, where the launch says so, they
-  // leave those to the gathered states.  Rows of part lines stay in the caches: past them a step
-  // at 48^3 x 37 took 0.22 ms (FP32) instead of 0.20.
-  constexpr bool LINES = MODE == 2 && FULL && LPC * APL * sizeof(T) % 64 == 0;
   constexpr int P = Ang::P;
-  constexpr int U = rt_batch<T, APL, PAIRED>::U;
+  constexpr int U = rt_batch<T, APL, PAIRED, STATES>::U;
   constexpr int CPB = RT_BLOCK / LPC;
   extern __shared__ __align__(16) unsigned char rt_smem[];
   V4 *s_an = (V4 *)rt_smem;
@@ -98,8 +130,7 @@ k_step(rt_step_args a, int64_t nblk) {
   const int k_single = Ang::SINGLE ? ang.k[P - 1] : ang.k[0];
   const T *Iin_lane = Iin + ang.k[0], *Iin_single = Iin + k_single;
   T Ic[APL];
-  if (LINES && a.past_caches) ang.template read_lane<true>(Iin_lane + row, Iin_single + row, Ic);
-  else ang.read_lane(Iin_lane + row, Iin_single + row, Ic);
+  ang.template read_lane<PAST>(Iin_lane + row, Iin_single + row, Ic);
 
   double Vnew = 0.0, Vstart = 0.0;
   // the start-of-step volume: the reverse modes take it from the forward step's tape
@@ -186,7 +217,7 @@ k_step(rt_step_args a, int64_t nblk) {
       V4 own[APL];
 #pragma unroll
       for (int q = 0; q < APL; ++q) own[q] = S::load(of((uint32_t)cell) + at(q), KK);
-      constexpr int UP = rt_batch<T, APL, PAIRED>::PLM;
+      constexpr int UP = rt_batch<T, APL, PAIRED, STATES>::PLM;
       for (int h = h0; h < h1; h += UP) {
         uint32_t j[UP];
         V4 r[UP], r0[UP], r1[UP];
@@ -208,37 +239,56 @@ k_step(rt_step_args a, int64_t nblk) {
 #pragma unroll
           for (int q = 0; q < P; ++q) g[u][q] = fma(az, ang.z[q], fma(ay, ang.y[q], fma(ax, ang.x[q], nb)));
         }
-        V4 x[UP][P];
+        V4 x[UP][P], x2[UP][P];  // x2: set, and used, where a pair's other state is needed
+        bool more[UP];           // a face fast enough that both directions of a pair enter through it
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
           const typename S::part *n = of(j[u]), *anti = n + LPC * P;
+          more[u] = false;
 #pragma unroll
-          for (int q = 0; q < P; ++q) x[u][q] = S::load((PAIRED && !(g[u][q] < T(0)) ? anti : n) + at(q), KK);
+          for (int q = 0; q < P; ++q) {
+            const bool in = g[u][q] < T(0), in2 = m2b[u] - g[u][q] < T(0);
+            x[u][q] = S::load((PAIRED && STATES < 2 && !in ? anti : n) + at(q), KK);
+            if (PAIRED && STATES == 2) x2[u][q] = S::load(anti + at(q), KK);
+            more[u] |= PAIRED && in && in2;
+          }
+          if (PAIRED && STATES == 1 && more[u]) {
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+              if (g[u][q] < T(0) && m2b[u] - g[u][q] < T(0)) x2[u][q] = S::load(anti + at(q), KK);
+          }
         }
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
           // the states of the face's two sides
           auto here = [&](const V4 &o) { return o.x + o.y * r0[u].x + o.z * r0[u].y + o.w * r0[u].z; };
           auto there = [&](const V4 &o) { return o.x + o.y * r0[u].w + o.z * r1[u].x + o.w * r1[u].y; };
-          bool more = false;  // a face fast enough that both directions of a pair enter through it
+          // In forms 1 and 2 both are formed before one is taken: a select between expressions becomes
+          // a branch around the fetches behind them (0.82 of the speed in form 2)
+          auto upwind = [&](bool in, T n, const V4 &o) {
+            if constexpr (STATES == 0) return in ? n : here(o);
+            const T f = here(o);
+            return in ? n : f;
+          };
 #pragma unroll
           for (int q = 0; q < P; ++q) {
             const T n = there(x[u][q]);
             const bool in = g[u][q] < T(0);
-            acc[q] -= g[u][q] * (in ? n : here(own[q]));
+            acc[q] -= g[u][q] * upwind(in, n, own[q]);
             if (PAIRED) {
               const T g2 = m2b[u] - g[u][q];  // the antipodal angle, as in the upwind loop
-              const bool in2 = g2 < T(0), both = in && in2;
-              const T to = acc[q + P] - g2 * (in2 ? n : here(own[q + P]));
+              const T n2 = STATES == 2 ? there(x2[u][q]) : n;
+              const bool in2 = g2 < T(0), both = STATES < 2 && in && in2;
+              const T to = acc[q + P] - g2 * upwind(in2, n2, own[q + P]);
               acc[q + P] = both ? acc[q + P] : to;
-              more |= both;
             }
           }
-          if (PAIRED && more) {
+          if (PAIRED && STATES < 2 && more[u]) {
 #pragma unroll
             for (int q = 0; q < P; ++q) {
               const T g2 = m2b[u] - g[u][q];
-              if (g[u][q] < T(0) && g2 < T(0)) acc[q + P] -= g2 * there(S::load(of(j[u]) + at(q + P), KK));
+              if (g[u][q] < T(0) && g2 < T(0))
+                acc[q + P] -= g2 * there(STATES == 1 ? x2[u][q] : S::load(of(j[u]) + at(q + P), KK));
             }
           }
         }
@@ -278,8 +328,7 @@ k_step(rt_step_args a, int64_t nblk) {
 
   {
     T *o = (T *)a.I_out + row;
-    if (LINES && a.past_caches) ang.template write_lane<true>(o + ang.k[0], o + k_single, Ic);
-    else ang.write_lane(o + ang.k[0], o + k_single, Ic);
+    ang.template write_lane<PAST>(o + ang.k[0], o + k_single, Ic);
   }
   if ((MODE == 1 || MODE == 2) && l == 0 && a.vol_out) a.vol_out[cell] = Vnew;
   if (MODE == 1 && l == 0 && a.src_tape_out) a.src_tape_out[RT_SRC_TAPE * cell + RT_TAPE_V] = Vstart;
@@ -288,6 +337,31 @@ k_step(rt_step_args a, int64_t nblk) {
 size_t rt_step_lds(int mode, size_t v4, int hf_cap) {
   const bool faces = mode >= 1 && mode <= 4;
   return faces ? ((mode == 2 ? 3 : 1) * v4 + sizeof(int32_t)) * (size_t)hf_cap : 0;
+}
+
+template <typename T, int LPC, int APL, bool FULL, int PAIRED>
+hipError_t launch_plm(const rt_step_args &a, int64_t nblk, dim3 grid, size_t smem, hipStream_t s) {
+  const dim3 block(RT_BLOCK);
+  const bool past = rt_whole_lines<T, LPC, APL, FULL>() &&
+                    (a.N > RT_PAST_CELLS || (int64_t)sizeof(T) * a.N * a.K > RT_PAST_BYTES);
+  const int states = PAIRED ? rt_states<T>(LPC, APL, nblk) : 0;
+  // only the forms rt_states can choose for this layout are built
+  constexpr bool BOTH = PAIRED && sizeof(T) == 4;
+  constexpr bool AHEAD = PAIRED && (sizeof(T) == 4 ? APL >= 8 || LPC == 4 : APL == 8 || APL == 10);
+  constexpr bool BEHIND = !PAIRED || sizeof(T) == 8 || LPC == 8;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, smem, s, a, nblk);
+    return hipGetLastError();
+  };
+  if constexpr (BOTH)
+    if (states == 2) return launch(k_step<T, LPC, APL, 2, FULL, PAIRED, 2>);
+  if constexpr (AHEAD)
+    if (states == 1) return launch(k_step<T, LPC, APL, 2, FULL, PAIRED, 1>);
+  if constexpr (BEHIND)
+    if (states == 0 && !past) return launch(k_step<T, LPC, APL, 2, FULL, PAIRED>);
+  if constexpr (rt_whole_lines<T, LPC, APL, FULL>())
+    if (states == 0 && past) return launch(k_step<T, LPC, APL, 2, FULL, PAIRED, 0, true>);
+  return hipErrorInvalidValue;
 }
 
 // Staging needs (records per half-face) x (half-faces of the largest range of the
@@ -303,17 +377,12 @@ hipError_t launch_mode(const rt_step_args &args, hipStream_t s) {
   const int64_t cpb = RT_BLOCK / LPC;
   const int64_t nblk = (a.N + cpb - 1) / cpb;
   const dim3 grid((unsigned)rt_grid_for(nblk)), block(RT_BLOCK);
-  // Rows that fit in the L2s (eight of 4 MB) are read back from there by the next half step, which
-  // gathers each about 16 times.  Two PLM steps, past the caches or through them: FP32 K = 80
-  // 32^3 (10 MB) 0.192 or 0.190 ms, 40^3 (20 MB) 0.315 or 0.310, 48^3 (35 MB) 0.538 or 0.549; FP64
-  // 32^3 (21 MB) 0.317 or 0.310, 48^3 (71 MB) 1.080 or 1.088, 64^3 (168 MB) 2.486 or 2.502.
-  a.past_caches = (int64_t)sizeof(T) * a.N * a.K > (int64_t)32 << 20;
   const size_t smem = rt_step_lds(a.do_transport, sizeof(V4), a.hf_cap);
   if (smem > (size_t)a.lds_max) return hipErrorInvalidConfiguration;
   switch (a.do_transport) {
     case 0: hipLaunchKernelGGL((k_step<T, LPC, APL, 0, FULL, PAIRED>), grid, block, smem, s, a, nblk); break;
     case 1: hipLaunchKernelGGL((k_step<T, LPC, APL, 1, FULL, PAIRED>), grid, block, smem, s, a, nblk); break;
-    case 2: hipLaunchKernelGGL((k_step<T, LPC, APL, 2, FULL, PAIRED>), grid, block, smem, s, a, nblk); break;
+    case 2: return launch_plm<T, LPC, APL, FULL, PAIRED>(a, nblk, grid, smem, s);
     case 3: hipLaunchKernelGGL((k_step<T, LPC, APL, 3, FULL, PAIRED>), grid, block, smem, s, a, nblk); break;
     case 4: hipLaunchKernelGGL((k_step<T, LPC, APL, 4, FULL, PAIRED>), grid, block, smem, s, a, nblk); break;
     case 5: hipLaunchKernelGGL((k_step<T, LPC, APL, 5, FULL, PAIRED>), grid, block, smem, s, a, nblk); break;

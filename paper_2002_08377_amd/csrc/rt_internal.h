@@ -90,7 +90,6 @@ struct rt_step_args {
   double a_4pi;       // a / 4 pi
   int paired;        // rt_pair_kind of the angle layout
   int hf_cap;        // LDS staging slots of the launched kernel (set at dispatch)
-  bool past_caches;  // PLM stage 2: its own rows bypass the caches (set at dispatch)
   int lds_max;       // LDS bytes a workgroup may use
   int hf_cap16, hf_cap32, hf_cap64;  // half-faces of the largest range of 16 / 32 / 64 cells
   const uint8_t *wg_order16, *wg_order32, *wg_order64;  // cell order within workgroups
