@@ -65,18 +65,21 @@ __global__ __launch_bounds__(RT_BLOCK) void k_diag(int64_t N, int K, const doubl
     double V[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      // past the last cell: that cell again, with no volume
+      // past the last cell: that cell again
       const int64_t c = c0 + r * CPB + threadIdx.x / LPC, cell = c < N ? c : N - 1;
-      V[r] = c < N ? vol[cell] : 0.0;
+      V[r] = vol[cell];
 #pragma unroll
       for (int q = 0; q < APL; ++q) x[r][q] = I[cell * (int64_t)K + ang.k[q]];
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+      // what is read again (past the last cell, and angle 0 in a slot past K, the last of a lane)
+      // is left out, not multiplied by zero: an infinite one would make the totals NaN
+      if (c0 + r * CPB + threadIdx.x / LPC >= N) continue;
       double t = 0, tx = 0, ty = 0, tz = 0;
 #pragma unroll
       for (int q = 0; q < APL; ++q) {
-        const double wx = ang.w[q] * (double)x[r][q];
+        const double wx = q + 1 < APL || ang.ok[q] ? ang.w[q] * (double)x[r][q] : 0.0;
         t += wx;
         tx += wx * ang.dx[q];
         ty += wx * ang.dy[q];
@@ -88,7 +91,7 @@ __global__ __launch_bounds__(RT_BLOCK) void k_diag(int64_t N, int K, const doubl
       Fy += V[r] * ty;
       Fz += V[r] * tz;
       // a non-finite intensity leaves t non-finite, whatever its weight
-      if (!isfinite(t) && c0 + r * CPB + threadIdx.x / LPC < N)
+      if (!isfinite(t))
         for (int q = 0; q < APL; ++q) bad += ang.ok[q] && !isfinite(x[r][q]);
     }
   }
