@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "rt_device.h"
+#include "rt_scan.h"
 
 // Scratch of the loss that allocates nothing: the per-workgroup partial sums in its first
 // RT_NOALLOC_PARTIALS doubles, the first fold in the last RT_BLOCK.  Each device holds
@@ -177,28 +178,26 @@ __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32
   if (threadIdx.x == 0) s_mark = 0;
   __syncthreads();
   {
-    const int h1 = s_rows[nc];
     constexpr int B = 4;  // ids, then weights, fetched together
-    for (int hb = s_rows[0] + threadIdx.x; hb < h1; hb += B * RT_BLOCK) {
+    rt_scan_half_faces<RT_BLOCK, B>(s_rows[0], s_rows[nc], threadIdx.x, [&](const uint32_t (&h)[B]) {
       int32_t fc[B];
       double u[B];
 #pragma unroll
-      for (int b = 0; b < B; ++b) fc[b] = hf_face[hb + b * RT_BLOCK < h1 ? hb + b * RT_BLOCK : hb];
+      for (int b = 0; b < B; ++b) fc[b] = hf_face[h[b]];
 #pragma unroll
       for (int b = 0; b < B; ++b) u[b] = face_weight[fc[b] >= 0 ? fc[b] : -(int64_t)fc[b] - 1];
 #pragma unroll
       for (int b = 0; b < B; ++b)
         if (u[b] != 0.0) {
-          const int h = hb + b * RT_BLOCK < h1 ? hb + b * RT_BLOCK : hb;
-          int c = 0, past = nc;  // rows[c] <= h < rows[past]
+          int c = 0, past = nc;  // rows[c] <= h[b] < rows[past]
           while (past - c > 1) {
             const int mid = (c + past) / 2;
-            if (s_rows[mid] <= h) c = mid;
+            if ((uint32_t)s_rows[mid] <= h[b]) c = mid;
             else past = mid;
           }
           atomicOr(&s_mark, 1ull << c);
         }
-    }
+    });
   }
   __syncthreads();
   const unsigned long long mark = s_mark;
@@ -220,8 +219,8 @@ __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32
     double sd[APL], Iv[APL];
     for (int q = 0; q < APL; ++q) sd[q] = Iv[q] = 0.0;
     for (int q = 0; q < APL; ++q) Iv[q] = ang.ok[q] ? (double)I[row + ang.k[q]] : 0.0;
-    const int h1 = s_rows[c + 1];
-    for (int hb = s_rows[c]; hb < h1; hb += LPC) {
+    const uint32_t h1 = s_rows[c + 1];  // unsigned, as in rt_scan_half_faces
+    for (uint32_t hb = s_rows[c]; hb < h1; hb += LPC) {
       double u = 0.0;
       double4 an = {0.0, 0.0, 0.0, 0.0};
       if (hb + l < h1) {
