@@ -154,14 +154,21 @@ hipError_t reduce_partials(const double *partial, int64_t nrows, unsigned min_ma
 // u_f sigma 4 pi c W_k (A n_out . n_k) I to its partial loss and that coefficient to
 // its seed; sigma = -1 on a face's second cell since n_out = -n_f there.
 // A loss weights few faces (a plane's: 1% of the cells at 96^3), so what bounds it is finding
-// them.  A workgroup of RT_LOSS_CELLS consecutive cells first reads the weights of its
+// them.  A workgroup of CELLS consecutive cells first reads the weights of its
 // half-faces, one thread each (they are one contiguous range), marks the cells that have one
 // and ends there when none has.  The lanes of a marked cell then read one face each, with its
 // record, and take the weighted ones in face order.  With every lane of every cell reading
 // all its faces it took 400 us at 96^3 x 80 with the caches cold, now 80 (its 55 MB of
 // half-face ids and as much of weights: 24 us at the rate of a copy, 35 us without weights).
+// A marked cell is a word in LDS that every finder sets: as bits of one word, set by atomics, their
+// queue doubled the time where many faces have a weight (all of them, 12^3 x 24: 29 us with atomics,
+// 13 without; 96^3 x 80 905 and 742).  CELLS is 64, or on meshes that leave fewer than
+// RT_LOSS_BLOCKS workgroups of that size as many as the lanes take at once (16 or 32), so that these
+// have no rounds over the marked cells (of 1024 workgroups the rounds are still the shorter:
+// 33^3 x 37 21 us against 23, a tenth of the faces weighted).
 #define RT_LOSS_CELLS 64
-template <typename T, int LPC, int APL>
+#define RT_LOSS_BLOCKS 256
+template <typename T, int LPC, int APL, int CELLS>
 __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32_t *row_ptr, const int32_t *hf_face,
                                                    const double4 *hf_an, const double *dirs, const double *W,
                                                    double c_light, const T *I, const double *face_weight,
@@ -169,13 +176,13 @@ __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32
   const int64_t lb = rt_logical_block(nblk);
   if (lb < 0) return;
   constexpr int CPB = RT_BLOCK / LPC;
-  static_assert(RT_LOSS_CELLS == 64, "one bit per cell");
-  __shared__ int s_rows[RT_LOSS_CELLS + 1];
-  __shared__ unsigned long long s_mark;
-  const int64_t w0 = lb * RT_LOSS_CELLS;
-  const int nc = (int)(N - w0 < RT_LOSS_CELLS ? N - w0 : RT_LOSS_CELLS);
+  static_assert(CELLS <= 64, "one bit per cell");
+  __shared__ int s_rows[CELLS + 1];
+  __shared__ int s_mark[64];  // whether a cell has a weighted face
+  const int64_t w0 = lb * CELLS;
+  const int nc = (int)(N - w0 < CELLS ? N - w0 : CELLS);
   if (threadIdx.x <= nc) s_rows[threadIdx.x] = row_ptr[w0 + threadIdx.x];
-  if (threadIdx.x == 0) s_mark = 0;
+  if (threadIdx.x < 64) s_mark[threadIdx.x] = 0;
   __syncthreads();
   {
     constexpr int B = 4;  // ids, then weights, fetched together
@@ -195,12 +202,12 @@ __global__ __launch_bounds__(RT_BLOCK) void k_loss(int64_t N, int K, const int32
             if ((uint32_t)s_rows[mid] <= h[b]) c = mid;
             else past = mid;
           }
-          atomicOr(&s_mark, 1ull << c);
+          s_mark[c] = 1;  // every writer writes this
         }
     });
   }
   __syncthreads();
-  const unsigned long long mark = s_mark;
+  const unsigned long long mark = __ballot(s_mark[threadIdx.x % 64] != 0);
   if (mark == 0) {
     if (threadIdx.x == 0) partial[lb] = 0.0;
     return;
@@ -535,11 +542,12 @@ template <typename T, int LPC, int APL>
 hipError_t launch_loss(const rt_mesh *m, int K, const double *dirs, const double *W, double c_light, const void *I,
                        const double *fw, double *loss, void *seed, double *partial, double *mid, int64_t cap,
                        hipStream_t s) {
-  const int64_t nblk = (m->N + RT_LOSS_CELLS - 1) / RT_LOSS_CELLS;
+  const int64_t wide = (m->N + RT_LOSS_CELLS - 1) / RT_LOSS_CELLS, cpb = RT_BLOCK / LPC;
+  const int64_t nblk = wide < RT_LOSS_BLOCKS ? (m->N + cpb - 1) / cpb : wide;
   if (nblk > cap) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_loss<T, LPC, APL>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK), 0, s, m->N, K,
-                     m->row_ptr, m->hf_face, m->hf_an64, dirs, W, c_light, (const T *)I, fw, (T *)seed, partial,
-                     nblk);
+  auto kernel = wide < RT_LOSS_BLOCKS ? k_loss<T, LPC, APL, RT_BLOCK / LPC> : k_loss<T, LPC, APL, RT_LOSS_CELLS>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK), 0, s, m->N, K, m->row_ptr, m->hf_face,
+                     m->hf_an64, dirs, W, c_light, (const T *)I, fw, (T *)seed, partial, nblk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return reduce_partials<1>(partial, nblk, 0u, mid, loss, s);
