@@ -37,10 +37,11 @@ template <typename T, int APL, int PAIRED, int STATES> struct rt_batch {
 //   K = 48  12^3: (0) 1.00 / .96 (1) .99 / .98 (2) 1.03 / 1.04   32^3: 1.08 / 1.07, 1.03 / 1.02, 1.02 / 1.02
 //   K = 24  12^3: (0) 1.00 / .96 (1) .99 / .98 (2) 1.03 / 1.03   64^3: 1.02 / .98, 1.01 / 1.00, 1.00 / 1.00
 // With four lanes per cell a wave holds twice the faces, and (0) nearly always fetches twice.
-// FP64 K = 80, 12^3: (0) 1.04 / .97 (1) 1.03 / .99, 24^3: 1.10 / 1.06, 1.06 / 1.05; (2) spills.
-template <typename T> constexpr int rt_states(int lpc, int apl, int64_t nblk) {
+// FP64 K = 80, antipodes side by side, 12^3: (0) 1.04 / .97 (1) 1.03 / .99, 24^3: 1.10 / 1.06, 1.06 / 1.05;
+// K/2 apart 12^3: 1.32 / 1.24, 1.27 / 1.21; (2) spills.
+template <typename T> constexpr int rt_states(int lpc, int apl, int paired, int64_t nblk) {
   const int64_t per_cu = (nblk + 255) / 256;  // workgroups
-  if (sizeof(T) == 8) return (apl == 8 || apl == 10) && per_cu <= 1 ? 1 : 0;
+  if (sizeof(T) == 8) return paired == 2 && (apl == 8 || apl == 10) && per_cu <= 1 ? 1 : 0;
   if (per_cu <= (apl >= 8 ? 1 : 2)) return 2;
   return lpc == 4 || (apl >= 8 && per_cu <= 10) ? 1 : 0;
 }
@@ -344,10 +345,10 @@ hipError_t launch_plm(const rt_step_args &a, int64_t nblk, dim3 grid, size_t sme
   const dim3 block(RT_BLOCK);
   const bool past = rt_whole_lines<T, LPC, APL, FULL>() &&
                     (a.N > RT_PAST_CELLS || (int64_t)sizeof(T) * a.N * a.K > RT_PAST_BYTES);
-  const int states = PAIRED ? rt_states<T>(LPC, APL, nblk) : 0;
+  const int states = PAIRED ? rt_states<T>(LPC, APL, PAIRED, nblk) : 0;
   // only the forms rt_states can choose for this layout are built
   constexpr bool BOTH = PAIRED && sizeof(T) == 4;
-  constexpr bool AHEAD = PAIRED && (sizeof(T) == 4 ? APL >= 8 || LPC == 4 : APL == 8 || APL == 10);
+  constexpr bool AHEAD = PAIRED && (sizeof(T) == 4 ? APL >= 8 || LPC == 4 : PAIRED == 2 && (APL == 8 || APL == 10));
   constexpr bool BEHIND = !PAIRED || sizeof(T) == 8 || LPC == 8;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, smem, s, a, nblk);
