@@ -374,7 +374,9 @@ struct rt_source_only {
   }
 };
 
-// hipErrorInvalidConfiguration: the step takes its separate launches.
+// hipErrorInvalidConfiguration: the paired layout does not fit and the general one is tried (on
+// meshes of 50 to 200 faces per cell 1.0 to 1.4 times as fast as the separate launches in the
+// paired layout), or that does not either and the step takes its separate launches.
 struct rt_whole_step {
   rt_step_args t;
   rt_kT_args a;

@@ -9,6 +9,7 @@
 //  pass 2, per group: the row is read again and updated, I' = I r + (r / Gamma^3) y S_g
 //    with S_g = kP_g a T^4/4pi + ks_g J~_g, and the radiation energy and momentum lost
 //    by the stored values (weighted by Wg) go to the gas.
+#include "rt_mg_rule.h"
 #include "rt_step_common.h"
 
 namespace {
@@ -431,7 +432,8 @@ struct rt_source_only {
   }
 };
 
-// hipErrorInvalidConfiguration: the step takes its separate launches.
+// hipErrorInvalidConfiguration: the paired layout does not fit and the general one is tried, or
+// that does not either (or is the slower one, rt_mg_rule.h) and the step takes its separate launches.
 struct rt_whole_step {
   rt_step_args a;
   rt_mg_args m;
@@ -449,6 +451,10 @@ struct rt_whole_step {
     // separate launches take 0.83; two are still ahead of them (FP64, 4 groups, 48^3 x 80: 0.40
     // against 0.53 ms; FP32, 8 groups: 0.52 against 0.70).
     if (smem > (size_t)a.lds_max / 2) return hipErrorInvalidConfiguration;
+    // a set that has a paired layout, whose rows did not fit in it
+    if (!PAIRED && a.paired && rt_paired_lanes(a.K) &&
+        !rt_mg_general_step(LPC, APL, sizeof(T), a.N, smem, (size_t)a.lds_max))
+      return hipErrorInvalidConfiguration;
     // An output that outgrows the Infinity Cache is stored past the caches, to leave them to the
     // gathered rows (335 MB: 0.615 -> 0.602 ms; 8 groups, 283 MB: 0.553 -> 0.515).
     const bool past_caches = (int64_t)sizeof(T) * m.G * a.N * a.K > (int64_t)128 << 20;
