@@ -22,17 +22,68 @@ struct kT_eval {
   double kP, kJ, S1, SG, SI, D, f, fp;
 };
 
-// x^b for b = half2 / 2 with a whole |half2| <= 40 (the same for every thread), x > 0, by
-// repeated squaring of x or its reciprocal: within |b| + 3 ulp.
+// x^b for b = half2 / 2 with a whole |half2| <= 40 (the same for every thread), x > 0 (or 0 with
+// b > 0), by repeated squaring of x, its reciprocal or its reciprocal root, each value carried with its
+// rounding error (p + pl, x + xl): within an ulp.  Squaring plain doubles doubles their errors each
+// time, |b| + 3 ulp in all, where exp(b ln x) is within |b ln x| + 2, which is less near x = 1.
 __device__ __forceinline__ double rt_half_power(double x, int half2) {
-  if (half2 < 0) x = rt_rcp(x);
+  const double x0 = x;
   unsigned m = half2 < 0 ? -half2 : half2;
-  double p = m & 1u ? sqrt(x) : 1.0;
-  for (m >>= 1; m; m >>= 1) {
-    if (m & 1u) p *= x;
-    x *= x;
+  if (m == 0) return 1.0;
+  double xl = 0.0, p, pl;
+  if (m & 1u) {
+    double s = __builtin_amdgcn_rsq(x);
+    double e = fma(-(x * s), s, 1.0);
+    s = fma(s * e, fma(0.375, e, 0.5), s);
+    const double h = x * s, hl = fma(x, s, -h);  // h: the root
+    e = fma(-hl, s, fma(-h, s, 1.0));
+    const double sl = 0.5 * s * e;
+    if (half2 < 0) {
+      p = s;
+      pl = sl;
+      const double q = s * s;
+      xl = fma(s, s, -q) + 2.0 * s * sl;
+      x = q;
+    } else {
+      p = h;
+      pl = fma(x, sl, hl);
+    }
+    m >>= 1;
+  } else {
+    if (half2 < 0) {
+      const double r = rt_rcp(x);
+      xl = fma(-x, r, 1.0) * r;
+      x = r;
+    }
+    for (m >>= 1; !(m & 1u); m >>= 1) {
+      const double q = x * x;
+      xl = fma(x, x, -q) + 2.0 * x * xl;
+      x = q;
+    }
+    p = x;
+    pl = xl;
+    m >>= 1;
+    if (m) {
+      const double q = x * x;
+      xl = fma(x, x, -q) + 2.0 * x * xl;
+      x = q;
+    }
   }
-  return p;
+  while (m > 1u) {
+    if (m & 1u) {
+      const double q = p * x;
+      pl = fma(p, x, -q) + fma(p, xl, pl * x);
+      p = q;
+    }
+    m >>= 1;
+    const double q = x * x;
+    xl = fma(x, x, -q) + 2.0 * x * xl;
+    x = q;
+  }
+  if (m == 0) x = 1.0, xl = 0.0;
+  const double v = fma(p, x, fma(p, xl, pl * x));
+  if (half2 > 0 && x0 == 0.0) return 0.0;
+  return v == v ? v : p * x;  // an overflow leaves no remainder
 }
 
 // What bounds the kernel is FP64 vector issue: about five evaluations per cell, each over all
