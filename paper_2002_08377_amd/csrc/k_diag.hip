@@ -667,11 +667,6 @@ hipError_t rt_launch_flux_loss(const rt_mesh *m, int K, const double *dirs, cons
                               s);
 }
 
-int64_t rt_loss_blocks(int64_t N, int K) {
-  const int64_t cpb = (K % 16 == 0 || K > 64) ? RT_BLOCK / 16 : RT_BLOCK / 8;
-  return (N + cpb - 1) / cpb;
-}
-
 hipError_t rt_launch_flux_loss_noalloc(const rt_mesh *m, int K, const double *dirs, const double *W, double c_light,
                                        const void *I, const double *face_weight, double *loss, void *seed, int dtype,
                                        hipStream_t s) {

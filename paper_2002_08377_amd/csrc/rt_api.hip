@@ -759,10 +759,9 @@ int rt_flux_loss_noalloc(rt_mesh *m, const rt_params *p, const rt_angles *a, con
   int dev = -1;
   RT_HIP(hipGetDevice(&dev), "current device");
   if (dev != m->device) return fail(RT_EINVAL, "the mesh lives on device %d but device %d is current", m->device, dev);
-  const int64_t nblk = rt_loss_blocks(m->N, a->K);
-  if (nblk > RT_NOALLOC_PARTIALS)
-    return fail(RT_EINVAL, "%lld cells at K=%d need %lld partial sums; the static scratch holds %d",
-                (long long)m->N, a->K, (long long)nblk, RT_NOALLOC_PARTIALS);
+  if (m->N > rt_noalloc_cells(a->K))
+    return fail(RT_EINVAL, "%lld cells at K=%d: calls on the static scratch are held to %lld there", (long long)m->N,
+                a->K, (long long)rt_noalloc_cells(a->K));
   hipError_t e = rt_launch_flux_loss_noalloc(m, a->K, a->dir, a->weight, p->c_light, I, face_weight, loss, seed,
                                              p->dtype, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "loss kernel launch (static scratch)");

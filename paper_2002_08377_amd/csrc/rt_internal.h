@@ -258,9 +258,11 @@ hipError_t rt_launch_flux_loss(const rt_mesh *m, int K, const double *dirs, cons
 // partial sums in a static device array of RT_NOALLOC_PARTIALS + RT_BLOCK doubles (2 MiB).
 #define RT_NOALLOC_PARTIALS ((1 << 18) - RT_BLOCK)
 #define RT_MAX_DEVICES 64
-// What the limit of the static array is held against: one partial sum per 16 or 32 cells (a
-// loss launch writes fewer, one per 64).
-int64_t rt_loss_blocks(int64_t N, int K);
+// The largest mesh of a call on it: one partial sum per 16 or 32 cells, what small meshes take (large
+// ones take one per 64; the limit is the interface's and does not follow the launch).
+static inline int64_t rt_noalloc_cells(int K) {
+  return (int64_t)RT_NOALLOC_PARTIALS * (K % 16 == 0 || K > 64 ? 16 : 32);
+}
 hipError_t rt_launch_flux_loss_noalloc(const rt_mesh *m, int K, const double *dirs, const double *W, double c_light,
                                        const void *I, const double *face_weight, double *loss, void *seed, int dtype,
                                        hipStream_t s);
