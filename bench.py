@@ -66,6 +66,7 @@ def algorithmic_ops(N, F, K):
 
 # The sources the step kernel is compiled from: its file and every header it includes.
 STEP_KERNEL_SOURCES = ("paper_2002_08377_amd/csrc/k_step.hip", "paper_2002_08377_amd/csrc/rt_step_common.h",
+                       "paper_2002_08377_amd/csrc/rt_source_vjp.h", "paper_2002_08377_amd/csrc/rt_face_speed.h",
                        "paper_2002_08377_amd/csrc/rt_device.h", "paper_2002_08377_amd/csrc/rt_internal.h",
                        "include/rtmm.h")
 

@@ -3,6 +3,7 @@
 // angles.  One pass reads the cell's intensity row, gathers the neighbour rows of
 // its faces through the half-face index (no atomics), updates the charges, runs the
 // source on the transported row while it is in registers, and writes the row once.
+#include "rt_face_speed.h"
 #include "rt_source_vjp.h"
 #include "rt_step_common.h"
 
@@ -37,8 +38,8 @@ template <typename T, int APL, int PAIRED, int STATES> struct rt_batch {
 //   K = 48  12^3: (0) 1.00 / .96 (1) .99 / .98 (2) 1.03 / 1.04   32^3: 1.08 / 1.07, 1.03 / 1.02, 1.02 / 1.02
 //   K = 24  12^3: (0) 1.00 / .96 (1) .99 / .98 (2) 1.03 / 1.03   64^3: 1.02 / .98, 1.01 / 1.00, 1.00 / 1.00
 // With four lanes per cell a wave holds twice the faces, and (0) nearly always fetches twice.
-// FP64 K = 80, antipodes side by side, 12^3: (0) 1.04 / .97 (1) 1.03 / .99, 24^3: 1.10 / 1.06, 1.06 / 1.05;
-// K/2 apart 12^3: 1.32 / 1.24, 1.27 / 1.21; (2) spills.
+// FP64 K = 80, antipodes side by side, 12^3: (0) 1.04 / .96 (1) 1.04 / .99, 20^3: 1.03 / .98, 1.02 / 1.00,
+// 24^3: 1.10 / 1.06, 1.06 / 1.05; K/2 apart 12^3: 1.32 / 1.24, 1.27 / 1.21; (2) spills.
 template <typename T> constexpr int rt_states(int lpc, int apl, int paired, int64_t nblk) {
   const int64_t per_cu = (nblk + 255) / 256;  // workgroups
   if (sizeof(T) == 8) return paired == 2 && (apl == 8 || apl == 10) && per_cu <= 1 ? 1 : 0;
@@ -73,13 +74,15 @@ template <typename T, int LPC, int APL, bool FULL> constexpr bool rt_whole_lines
 // The cells of a workgroup are consecutive, so their half-faces form one contiguous
 // range; it is staged in LDS (dynamic size: the largest range of any workgroup,
 // found at upload) and the face loops read their records from there.
-// Occupancy target: the FP64 PLM stage 2 takes 252 registers, two waves per SIMD, and is held
-// to that.  Everything else keeps the compiler's choice.
-template <typename T, int MODE> struct rt_step_waves {
-  static constexpr int value = MODE == 2 && sizeof(T) == 8 ? 2 : 1;
+// Occupancy target: the FP64 PLM stage 2 is held to two waves per SIMD (10 angles per lane: 248
+// registers; unpaired forms of 6 to 8 angles and 12 paired spill 16 to 44), except the form of
+// small grids, which have one (held to two it spills 30 values: 12^3 x 80, two steps 93 us, now 88).
+// Everything else keeps the compiler's choice.
+template <typename T, int MODE, int STATES> struct rt_step_waves {
+  static constexpr int value = MODE == 2 && sizeof(T) == 8 && STATES == 0 ? 2 : 1;
 };
 template <typename T, int LPC, int APL, int MODE, bool FULL, int PAIRED, int STATES = 0, bool PAST = false>
-__global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_step_waves<T, MODE>::value))) void
+__global__ __launch_bounds__(RT_BLOCK) __attribute__((amdgpu_waves_per_eu(rt_step_waves<T, MODE, STATES>::value))) void
 k_step(rt_step_args a, int64_t nblk) {
   using V4 = typename rt_vec4<T>::type;
   // Runs of two pairs per lane (fewer, wider gathers): at 128^3 x 80 upwind, FP32 with
@@ -238,25 +241,36 @@ k_step(rt_step_args a, int64_t nblk) {
           const T ax = sc * r[u].x, ay = sc * r[u].y, az = sc * r[u].z, nb = -(sd * r[u].w);
           m2b[u] = nb + nb;
 #pragma unroll
-          for (int q = 0; q < P; ++q) g[u][q] = fma(az, ang.z[q], fma(ay, ang.y[q], fma(ax, ang.x[q], nb)));
+          for (int q = 0; q < P; ++q) g[u][q] = rt_face_speed(ax, ay, az, nb, ang.x[q], ang.y[q], ang.z[q]);
         }
+        // The antipode's speed: in FP64 with no rounding on top of that of g; in FP32 as in the upwind loop,
+        // written out where it is used (through a call the 12-angle form loses a wave per SIMD).
+        constexpr bool FP64 = sizeof(T) == 8;
+        T g2d[UP][P];
+        if (FP64)
+#pragma unroll
+          for (int u = 0; u < UP; ++u)
+#pragma unroll
+            for (int q = 0; q < P; ++q)
+              g2d[u][q] = rt_antipode_speed<T>(sc * r[u].x, sc * r[u].y, sc * r[u].z, -(sd * r[u].w), ang.x[q],
+                                               ang.y[q], ang.z[q]);
         V4 x[UP][P], x2[UP][P];  // x2: set, and used, where a pair's other state is needed
         bool more[UP];           // a face fast enough that both directions of a pair enter through it
 #pragma unroll
         for (int u = 0; u < UP; ++u) {
-          const typename S::part *n = of(j[u]), *anti = n + LPC * P;
+          const typename S::part *n = of(j[u]), *across = n + LPC * P;
           more[u] = false;
 #pragma unroll
           for (int q = 0; q < P; ++q) {
-            const bool in = g[u][q] < T(0), in2 = m2b[u] - g[u][q] < T(0);
-            x[u][q] = S::load((PAIRED && STATES < 2 && !in ? anti : n) + at(q), KK);
-            if (PAIRED && STATES == 2) x2[u][q] = S::load(anti + at(q), KK);
+            const bool in = g[u][q] < T(0), in2 = (FP64 ? g2d[u][q] : m2b[u] - g[u][q]) < T(0);
+            x[u][q] = S::load((PAIRED && STATES < 2 && !in ? across : n) + at(q), KK);
+            if (PAIRED && STATES == 2) x2[u][q] = S::load(across + at(q), KK);
             more[u] |= PAIRED && in && in2;
           }
           if (PAIRED && STATES == 1 && more[u]) {
 #pragma unroll
             for (int q = 0; q < P; ++q)
-              if (g[u][q] < T(0) && m2b[u] - g[u][q] < T(0)) x2[u][q] = S::load(anti + at(q), KK);
+              if (g[u][q] < T(0) && (FP64 ? g2d[u][q] : m2b[u] - g[u][q]) < T(0)) x2[u][q] = S::load(across + at(q), KK);
           }
         }
 #pragma unroll
@@ -277,7 +291,7 @@ k_step(rt_step_args a, int64_t nblk) {
             const bool in = g[u][q] < T(0);
             acc[q] -= g[u][q] * upwind(in, n, own[q]);
             if (PAIRED) {
-              const T g2 = m2b[u] - g[u][q];  // the antipodal angle, as in the upwind loop
+              const T g2 = FP64 ? g2d[u][q] : m2b[u] - g[u][q];
               const T n2 = STATES == 2 ? there(x2[u][q]) : n;
               const bool in2 = g2 < T(0), both = STATES < 2 && in && in2;
               const T to = acc[q + P] - g2 * upwind(in2, n2, own[q + P]);
@@ -287,7 +301,7 @@ k_step(rt_step_args a, int64_t nblk) {
           if (PAIRED && STATES < 2 && more[u]) {
 #pragma unroll
             for (int q = 0; q < P; ++q) {
-              const T g2 = m2b[u] - g[u][q];
+              const T g2 = FP64 ? g2d[u][q] : m2b[u] - g[u][q];
               if (g[u][q] < T(0) && g2 < T(0))
                 acc[q + P] -= g2 * there(STATES == 1 ? x2[u][q] : S::load(of(j[u]) + at(q + P), KK));
             }
