@@ -22,8 +22,9 @@ namespace {
 // are gathered two faces per batch, all loads of a batch issued before any is used.
 // Output: the limited gradient as [N][3][K] (PACKED false), or, for the PLM step's own
 // stage 2, each cell and angle's face state (phi, alpha grad phi) in 16-byte parts (PACKED
-// true; with split = K/2 the states of angles 0, 2, 4, ... first, then those of 1, 3, 5, ...).  Bound by the address units of its gathers (FP64 64^3 x 80: 0.29 of 0.39 ms) and the
-// bytes of its output; in a full layout (K = LPC APL) a neighbour's elements sit at compile-time
+// true; with split = K/2 the states of angles 0, 2, 4, ... first, then those of 1, 3, 5, ...).
+// Bound by the address units of its gathers (FP64 64^3 x 80: 0.29 of 0.39 ms) and the bytes of its
+// output; in a full layout (K = LPC APL) a neighbour's elements sit at compile-time
 // offsets from one 64-bit multiply-add per face (two PLM steps at 64^3 x 80, FP64 2.63 -> 2.54
 // ms).  Two or four consecutive angles per lane (fewer, wider gathers) spread its stores over
 // more lines: FP64 2.59 ms with two, FP32 1.34 -> 1.42 with two and 1.79 with four.
@@ -135,7 +136,8 @@ __global__ __launch_bounds__(RT_BLOCK) void k_gradient(int64_t N, int K, const i
     const int k = kk[q];
     if constexpr (PACKED) {
       using S = rt_state<T>;
-      const int at = split ? (k >> 1) + (k & 1 ? split : 0) : k;
+      // (asked in every FP64 layout: without the question 60^3 x 20 takes 983 us per two steps instead of 957)
+      const int at = (FULL || sizeof(T) == 8) && split ? (k >> 1) + (k & 1 ? split : 0) : k;
       typename S::part *o = (typename S::part *)G + S::PARTS * cell * K + at;
       if (FULL && past_caches) S::template store<true>(o, K, s[q], al * gx[q], al * gy[q], al * gz[q]);
       else S::template store<false>(o, K, s[q], al * gx[q], al * gy[q], al * gz[q]);
@@ -171,8 +173,12 @@ hipError_t launch_one(const rt_mesh *m, int K, const void *I, void *G, int split
 
 template <typename T, int LPC, int APL, bool PACKED>
 hipError_t launch(const rt_mesh *m, int K, const void *I, void *G, int split, hipStream_t s) {
-  return K == LPC * APL ? launch_one<T, LPC, APL, true, PACKED>(m, K, I, G, split, s)
-                        : launch_one<T, LPC, APL, false, PACKED>(m, K, I, G, split, s);
+  if (K == LPC * APL) return launch_one<T, LPC, APL, true, PACKED>(m, K, I, G, split, s);
+  // Sets that stage 2 takes in pairs fill their lanes here: 8, 24 and 40 angles eight lanes (whose records
+  // fit wherever stage 2's larger groups do), multiples of 16 sixteen.  So FP32 states are split in full layouts
+  // only (two steps, FP32: 40^3 x 90 410 -> 403 us, 33^3 x 90 256 -> 250).
+  if (split) return hipErrorInvalidValue;
+  return launch_one<T, LPC, APL, false, PACKED>(m, K, I, G, 0, s);
 }
 
 template <typename T, bool PACKED>
