@@ -94,13 +94,16 @@ __device__ __forceinline__ double rt_half_power(double x, int half2) {
 // terms, no cancellation, and r' of order one keeps the squares in range for any u.  A power
 // law with a whole or half-whole exponent is a few multiplications instead of log and exp.
 // The directions and weights come from LDS (read by every lane before and after the
-// iteration).  64^3 x 80, exponent -3.5: 272 -> 175 us in FP32 (the sums and powers alone 240;
-// one evaluation fewer at either end of the iteration 187; three waves per SIMD the rest).
+// iteration).  64^3 x 80, exponent -3.5, FP32, kernel alone, when each was made: 272 -> 175 us (the
+// sums and powers alone 240; one evaluation fewer at either end of the iteration 187; three waves per
+// SIMD the rest).  At 128^3 x 80 1.14 ms with plain powers, 1.15 with powers that round once.
 // HALF: both exponents are whole or half-whole numbers (rt_half_power).
 //
-// Waves per SIMD the register use is held to: three where the spill stays within a few values
-// (10 angles per lane: 8), against 198 registers and two waves (351 -> 340 us for the step
-// above); log and exp take 30 registers more, and there three waves spill 50 (411 against 370).
+// Waves per SIMD the register use is held to: three where the spill stays within a few values (4 to 11
+// here, at 10 angles per lane in pairs and at 8 without), against 196 to 228 registers and two waves.
+// Steps of unpaired sets at 8 angles per lane, three waves and two: 40^3 x 120 FP32 121 and 146 us,
+// FP64 134 and 150; 40^3 x 61 75 and 86, 76 and 84; 24^3 x 61 the same.  log and exp take 30 registers
+// more, and there three waves spill 50 (64^3 x 80 step, FP32: 411 against 370 us).
 template <int APL, int PAIRED, bool HALF> struct rt_kT_waves {
   static constexpr int value = HALF && (!PAIRED || APL <= 10) ? 3 : PAIRED && APL > 10 ? 1 : 2;
 };
@@ -336,8 +339,9 @@ k_source_kT(rt_kT_args a, int64_t nblk) {
 // intensities were written, read twice and written again, and the transport (bound by its
 // gathers) and the source (bound by FP64 issue) each left the other's unit idle.  The
 // transported values wait in LDS, in words of the lane's own, through the iteration.
-// 64^3 x 80, exponent -3.5, FP32: 350 -> 319 us; 12^3 x 24 FP64 24.4 -> 21.8.  FP64 rows of
-// 10 angles per lane gain only at two waves per SIMD (48^3 x 80: 172 -> 165 us; 173 at three).
+// A call at 64^3 x 80, exponent -3.5, FP32, its state reset included: 310 -> 274 us when it was made,
+// 269 now.  FP64 rows of 10 angles per lane take two waves per SIMD (198 registers), measured at K = 80:
+// 24^3 26.5 us against 28.7 with three, 48^3 131 against 128, 64^3 322 against 360.
 template <typename T, int APL, int PAIRED, bool HALF> struct rt_kT_step_waves {
   static constexpr int value = sizeof(T) == 8 && PAIRED && APL == 10 ? 2 : rt_kT_waves<APL, PAIRED, HALF>::value;
 };

@@ -201,8 +201,8 @@ __global__ __launch_bounds__(RT_BLOCK) void k_source_mg(rt_mg_args a, int64_t nb
 // Here JG groups share a sweep over the faces (their speeds, records and upwind tests are the
 // same), each group's transported row is summed on the spot, and the rows wait for the
 // temperature where the lane left them: the last sweep's in registers, the others in LDS, in
-// words of the lane's own (no other lane reads them).  0.818 -> 0.602 ms (FP32); FP64 at
-// 48^3 x 80 0.53 -> 0.38, 12^3 x 24 43 -> 27 us.  Bound now by the gathers and the vector
+// words of the lane's own (no other lane reads them).  A call, its state reset included: 0.80 ->
+// 0.59 ms (FP32); FP64 at 48^3 x 80 0.53 -> 0.38, 12^3 x 24 43 -> 27 us.  Bound now by the gathers and the vector
 // issue of the faces, at three waves per SIMD (FP32; held to four it spills and takes 0.69 ms).
 // groups whose rows wait in LDS: all but the last sweep's two (a lone group's waits there)
 __host__ __device__ constexpr int rt_mg_rows(int G) { return G > 2 ? G - 2 : G == 1 ? 1 : 0; }
@@ -456,7 +456,7 @@ struct rt_whole_step {
         !rt_mg_general_step(LPC, APL, sizeof(T), a.N, smem, (size_t)a.lds_max))
       return hipErrorInvalidConfiguration;
     // An output that outgrows the Infinity Cache is stored past the caches, to leave them to the
-    // gathered rows (335 MB: 0.615 -> 0.602 ms; 8 groups, 283 MB: 0.553 -> 0.515).
+    // gathered rows (kernel alone, 335 MB: 0.615 -> 0.602 ms; 8 groups, 283 MB: 0.553 -> 0.515).
     const bool past_caches = (int64_t)sizeof(T) * m.G * a.N * a.K > (int64_t)128 << 20;
     const int64_t nblk = (a.N + cpb - 1) / cpb;
     hipLaunchKernelGGL((k_step_mg<T, LPC, APL, FULL, PAIRED>), dim3((unsigned)rt_grid_for(nblk)), dim3(RT_BLOCK),

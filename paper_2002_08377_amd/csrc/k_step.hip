@@ -203,12 +203,11 @@ k_step(rt_step_args a, int64_t nblk) {
       // reconstructed face states of the half-step intensities (PLM stage 2).  Of an antipodal
       // pair only the direction that enters through a face needs the neighbour's state, so one
       // state per pair is gathered, chosen by the sign of the face speed, and the second where
-      // both enter.  The kernel is bound by the address and data units of its gathers (80% of the
-      // time, both precisions) and the L2 lines behind them: 64^3 x 80 step with antipodes K/2
+      // both enter.  The kernel is bound by its gathers: their address units are busy 68% of the
+      // time in either precision, and the L2 lines behind them add to it: 64^3 x 80 step with antipodes K/2
       // apart, FP64 1.64 -> 1.25 ms, side by side 1.38 -> 1.24; FP32 0.74 -> 0.69 and 0.71 -> 0.65.
       // Faces at a third of the light speed, where many pairs enter whole: FP32 0.323 -> 0.324 ms
-      // (48^3 x 80), FP64 0.72 -> 0.61.  Up to 20^3 cells, where a CU has one workgroup and waits
-      // for each face in turn, the choice lengthens the FP32 chain (12^3 x 80: 41.2 -> 42.5 us).
+      // (48^3 x 80), FP64 0.72 -> 0.61.  Small grids wait for each face in turn: rt_states.
       using S = rt_state<T>;
       const int KK = FULL ? LPC * APL : K;
       // a pair's states are K/2 apart in either order of the angles, so that lanes which pick the
